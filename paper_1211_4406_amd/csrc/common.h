@@ -93,6 +93,13 @@ constexpr uint32_t kPackCountMax = 0x3ffffffu;
 //   y = skip,
 // oct = the low bits of (ix, iy, iz) as x << 2 | y << 1 | z.
 constexpr uint32_t kWalkCountMax = 0x7fffffu;
+// and, in level-slot order (a cell's children side by side), into one
+// 16-byte record for the walk of one wave per group:
+//   x = ix | (a & 0x7ff) << 21,  y = iy | ((a >> 11) & 0x7ff) << 21,
+//   z = iz | ((a >> 22) & 0x3ff) << 21,  w = level | children << 5,
+// a = the slot of the first child, or a leaf's (children = 0) particle count.
+constexpr int64_t kWaveWalkGroups = 3 << 16;   // largest number of groups walked by waves (lists.hip)
+constexpr int64_t kWaveWalkCells = 1 << 30;    // and of cells (items are sorted as 31-bit keys)
 // A cell of a refitted tree for the list traversal, 32 bytes: the packed
 // record and its box rounded outward to multiples of q = 2^-(level + 10),
 // per axis a the 16-bit offsets (in q) of its lower and upper bound from
@@ -131,6 +138,7 @@ struct Tree {
     // particle; a cell's children are one run of the next level's slots):
     // first particle, preorder id and first child slot (-1 for a leaf)
     DevBuf<int32_t> sfirst, spre, schild;
+    DevBuf<uint4> srec;        // slot-ordered walk records (none past kWaveWalkGroups groups)
     DevBuf<double> clo, chi;   // [nn*3] boxes of the cells of a refitted tree
     DevBuf<RefitCell> rpack;   // their walk records
     // groups, in order of first
@@ -179,6 +187,19 @@ __device__ __forceinline__ int64_t xcd_block(int64_t b, int64_t nb) {
     const int64_t x = b & 7, y = b >> 3;
     const int64_t q = nb >> 3, r = nb & 7;
     return (x < r ? x * (q + 1) : r * (q + 1) + (x - r) * q) + y;
+}
+
+// Inclusive prefix sum over the 64 lanes of a wave, all of them active, in
+// six adds with DPP operands (a shuffle goes through the LDS crossbar, whose
+// latency such a chain of six would pay six times).
+__device__ __forceinline__ int wave_scan(int x) {
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);   // row_shr:1
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);   // row_shr:2
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);   // row_shr:4
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);   // row_shr:8
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);   // row_bcast:15
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);   // row_bcast:31
+    return x;
 }
 
 // ------------------------------------------------------------------ scan

@@ -32,6 +32,7 @@
 // margin of a threshold (classify32 below): the decisions, and so the
 // lists, are those of the FP64 expressions.
 #include <type_traits>
+#include <vector>
 
 #include "common.h"
 
@@ -176,6 +177,16 @@ __device__ __forceinline__ int classify32(int level, int leaf, const float* c, c
     return leaf ? 2 : 3;
 }
 
+struct Bounds32 {
+    float rc_hi, rc_lo, inv_th;
+};
+
+__device__ __forceinline__ Bounds32 bounds32(double rc2, double th2) {
+    const float rc2f = (float)rc2;
+    const float bp = 2.5e-6f * sqrtf(rc2f) + 2e-6f * rc2f + 1e-12f;
+    return {rc2f + bp, rc2f - bp, th2 > 0.0 ? (float)(1.0 / sqrt(th2)) : INFINITY};
+}
+
 __device__ __forceinline__ double refit_axis_gap(double cen, double cg, double half) {
     double t = cen - cg;
     t = fabs(t - rint(t));
@@ -223,6 +234,54 @@ __device__ __forceinline__ int classify_refit(const Cell& k, const double* bl, c
     return k.leaf ? 2 : 3;
 }
 
+// The class of the cell of a slot record (its preorder id `pre`), by the
+// tests of k_lists: FP32 first for a built tree, its rounded box for a
+// refitted one.
+template <bool COM, bool REFIT>
+__device__ __forceinline__ int classify_slot(const uint4& r, int level, bool leaf, int32_t pre,
+                                             const double* __restrict__ nX, const double* __restrict__ nY,
+                                             const double* __restrict__ nZ, const RefitCell* __restrict__ rpack,
+                                             const Frame& f, const Frame32& f32, const Bounds32& b32, double rc2,
+                                             double th2) {
+    const uint32_t ix = r.x & 0x1fffffu, iy = r.y & 0x1fffffu, iz = r.z & 0x1fffffu;
+    Cell k;
+    k.level = level;
+    k.leaf = leaf;
+    double com[3] = {0.0, 0.0, 0.0};
+    if (COM) {
+        com[0] = nX[pre];
+        com[1] = nY[pre];
+        com[2] = nZ[pre];
+    }
+    WalkPos w;
+    w.ix = ix;
+    w.iy = iy;
+    w.iz = iz;
+    if (REFIT) {
+        RefitCell rc;
+        rc.pk = r;
+        const int4 b = *reinterpret_cast<const int4*>(rpack[pre].b);
+        rc.b[0] = b.x;
+        rc.b[1] = b.y;
+        rc.b[2] = b.z;
+        rc.b[3] = b.w;
+        if (!(rc.b[3] & 1)) return leaf ? 2 : 3;
+        k.side = ldexp(1.0, -level);
+        double bl[3], bh[3];
+        refit_box(rc, k, bl, bh);
+        return classify_refit(k, bl, bh, com, COM, f, rc2, th2);
+    }
+    // (i + 1/2) 2^-level: exact in FP32 (i < 2^21)
+    const float side32 = __int_as_float((127 - level) << 23), hs32 = side32 * 0.5f;
+    const float c32[3] = {__fmaf_rn((float)ix, side32, hs32), __fmaf_rn((float)iy, side32, hs32),
+                          __fmaf_rn((float)iz, side32, hs32)};
+    const float m32[3] = {COM ? (float)com[0] : c32[0], COM ? (float)com[1] : c32[1], COM ? (float)com[2] : c32[2]};
+    const int cls = classify32(level, leaf, c32, m32, f32, b32.rc_hi, b32.rc_lo, b32.inv_th);
+    if (cls >= 0) return cls;
+    cell_geometry(k, w);
+    return classify(k, COM ? com : k.c, f, rc2, th2);
+}
+
 // Items of one group pass through a 16-slot LDS buffer of the thread and go
 // to memory as aligned 64-byte chunks (the partial chunks at the two ends of
 // a group's items are written item by item), so that the item array is
@@ -268,6 +327,11 @@ struct ItemWriter {
 // counted in totals[3], and the lists are then rebuilt with WRITE = true:
 // a second walk that stores the items of every group compactly at ioff).
 constexpr int64_t kSlot = 2048;
+// The totals (particle entries, cell entries, interactions, groups that did
+// not fit) are kept in kTotals rows of four, block b adding to row b mod
+// kTotals, and summed on the host: one row for all groups made the waves'
+// walk wait for its atomics (34 ns a group, 1.9 ms at 51000 groups).
+constexpr int kTotals = 256;
 constexpr int kListThreads = 64;   // one wave per block (128 and 256 measured slower)
 
 template <int G, bool WRITE, bool COM, bool REFIT>
@@ -306,10 +370,7 @@ __global__ __launch_bounds__(kListThreads) void k_lists(int64_t ng, const double
             f32[q].cg[a] = (float)f[q].cg[a];
             f32[q].hg[a] = (float)f[q].hg[a];
         }
-    const float rc2f = (float)rc2;
-    const float bp = 2.5e-6f * sqrtf(rc2f) + 2e-6f * rc2f + 1e-12f;
-    const float rc_hi = rc2f + bp, rc_lo = rc2f - bp;
-    const float inv_th = th2 > 0.0 ? (float)(1.0 / sqrt(th2)) : INFINITY;
+    const Bounds32 b32 = bounds32(rc2, th2);
     const uint64_t full = (1ull << G) - 1ull;
     uint64_t masks = valid;  // level 0
     int64_t i = valid ? 0 : nn;
@@ -362,7 +423,7 @@ __global__ __launch_bounds__(kListThreads) void k_lists(int64_t ng, const double
                 if (REFIT) {
                     cls = bounded ? classify_refit(k, bl, bh, mcen, COM, f[q], rc2, th2) : (k.leaf ? 2 : 3);
                 } else {
-                    cls = classify32(k.level, k.leaf, c32, mc32, f32[q], rc_hi, rc_lo, inv_th);
+                    cls = classify32(k.level, k.leaf, c32, mc32, f32[q], b32.rc_hi, b32.rc_lo, b32.inv_th);
                     if (cls < 0) {
                         if (!geom) {
                             cell_geometry(k, wpos);
@@ -421,10 +482,176 @@ __global__ __launch_bounds__(kListThreads) void k_lists(int64_t ng, const double
         d += __shfl_xor(d, o, 64);
     }
     if ((threadIdx.x & 63) == 0) {
+        totals += 4 * (blockIdx.x & (kTotals - 1));
         atomicAdd(&totals[0], a);
         atomicAdd(&totals[1], b);
         atomicAdd(&totals[2], c);
         if (d) atomicAdd(&totals[3], d);
+    }
+}
+
+// The same lists from one wave per group, for trees of at most
+// kWaveWalkGroups groups (the tree then has the slot-ordered records).  The wave keeps the cells its group still has to
+// look at on a stack in LDS, as level slots; it takes up to 64 of them at a
+// time, one per lane, and pushes the children of those it opens (they are
+// one run of the next level's slots, so their records are read side by
+// side).  Items are collected as they are found, at the other end of the
+// same LDS buffer, and put in preorder at the end by a bitonic sort in
+// registers: the order in which the thread's walk finds them.
+//
+// A thread's walk is a chain of dependent loads, one per visited cell: about
+// 1.1 ms for a clustered set of any size below 10^6 particles, with a wave
+// for 64 groups and most of the chip idle.  Here the chain is one load per 64
+// cells, and the waves are 64 times as many.
+// It issues more instructions per group (idle lanes in the top levels, the
+// sort), so that a tree that fills the chip with threads' walks keeps those.
+// k_lists against k_walk, us: 160 / 12 at 4096 uniform particles (96 groups),
+// 1117 / 49 at 131071 clustered ones (3050), 1564 / 436 at 2^21 (51000), 744
+// / 216 at 2^21 on the Zel'dovich lattice (33000), but 1563 / 1578 at 1.3e7
+// clustered (316000) and 1240 / 1660 at 2^24 on the lattice (265000); refitted
+// trees at 2^21: 933 / 331.  The line lies where the two would meet.
+// A group that does not fit the buffer is counted in totals[3] and leaves its
+// list empty; the thread's walk then does the whole tree.
+constexpr int kWaveBuf = 2304;   // items and stack together; 17 waves per CU
+constexpr int kWaveItems = 2048;
+static_assert(kWaveItems <= kSlot, "a wave's items fit a group's slot");
+
+// The value of lane ^ M.
+template <int M>
+__device__ __forceinline__ int lane_xor(int x) {
+    if (M == 1) return __builtin_amdgcn_mov_dpp(x, 0xb1, 0xf, 0xf, true);    // quad_perm:[1,0,3,2]
+    if (M == 2) return __builtin_amdgcn_mov_dpp(x, 0x4e, 0xf, 0xf, true);    // quad_perm:[2,3,0,1]
+    if (M == 8) return __builtin_amdgcn_mov_dpp(x, 0x128, 0xf, 0xf, true);   // row_ror:8
+    if (M == 32) return __shfl_xor(x, 32, 64);
+    return __builtin_amdgcn_ds_swizzle(x, (M << 10) | 0x1f);
+}
+
+template <int R, int K, int M>
+__device__ __forceinline__ void bitonic_step(int (&v)[R], int lane) {
+    // element e = lane R + r; ascending where bit K of e is clear
+    if constexpr (M >= R) {
+        const bool low = ((lane & (M / R)) == 0) == ((lane & (K / R)) == 0);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int o = lane_xor<M / R>(v[r]);
+            const int mn = v[r] < o ? v[r] : o, mx = v[r] < o ? o : v[r];
+            v[r] = low ? mn : mx;
+        }
+    } else {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            if (r & M) continue;
+            const bool up = K >= R ? (lane & (K / R)) == 0 : (r & K) == 0;
+            const int x = v[r], y = v[r | M];
+            const int mn = x < y ? x : y, mx = x < y ? y : x;
+            v[r] = up ? mn : mx;
+            v[r | M] = up ? mx : mn;
+        }
+    }
+    if constexpr (M > 1) bitonic_step<R, K, M / 2>(v, lane);
+}
+
+template <int R, int K>
+__device__ __forceinline__ void bitonic_merge(int (&v)[R], int lane) {
+    bitonic_step<R, K, K / 2>(v, lane);
+    if constexpr (K < 64 * R) bitonic_merge<R, 2 * K>(v, lane);
+}
+
+// n <= 64 R item keys (2 preorder + accepted) sorted, and written as items.
+template <int R>
+__device__ __forceinline__ void write_sorted(const int32_t* key, int n, int lane, int32_t* __restrict__ out) {
+    int v[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) v[r] = r * 64 + lane < n ? key[r * 64 + lane] : INT32_MAX;
+    bitonic_merge<R, 2>(v, lane);
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int32_t c = v[r] >> 1;
+        if (lane * R + r < n) out[lane * R + r] = (v[r] & 1) ? -c - 1 : c;
+    }
+}
+
+template <bool COM, bool REFIT>
+__global__ __launch_bounds__(64) void k_walk(int64_t ng, const double* __restrict__ glo,
+                                             const double* __restrict__ ghi, const int32_t* __restrict__ gcount,
+                                             const uint4* __restrict__ srec, const int32_t* __restrict__ spre,
+                                             const double* __restrict__ nX, const double* __restrict__ nY,
+                                             const double* __restrict__ nZ, const RefitCell* __restrict__ rpack,
+                                             double rc2, double th2, int64_t* __restrict__ cnt,
+                                             int64_t* __restrict__ icnt, unsigned long long* __restrict__ totals,
+                                             int32_t* __restrict__ items) {
+    __shared__ int32_t buf[kWaveBuf];   // items from the front, the stack from the back
+    const int lane = threadIdx.x;
+    const int64_t g = xcd_block(blockIdx.x, gridDim.x);
+    const Frame f = group_frame(glo, ghi, g);
+    Frame32 f32;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        f32.cg[a] = (float)f.cg[a];
+        f32.hg[a] = (float)f.hg[a];
+    }
+    const Bounds32 b32 = bounds32(rc2, th2);
+    const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+    totals += 4 * (blockIdx.x & (kTotals - 1));
+    int ni = 0, top = kWaveBuf - 1;   // the stack is buf[top, kWaveBuf)
+    uint32_t np = 0, nc = 0;
+    if (lane == 0) buf[top] = 0;   // the root is slot 0
+    __syncthreads();
+    while (top < kWaveBuf) {
+        const bool on = top + lane < kWaveBuf;
+        int cls = 0, kids = 0;
+        int32_t pre = 0;
+        uint32_t a = 0;
+        if (on) {
+            const int32_t slot = buf[top + lane];
+            const uint4 r = srec[slot];
+            pre = spre[slot];
+            const int level = (int)(r.w & 31u);
+            kids = (int)(r.w >> 5);
+            a = (r.x >> 21) | ((r.y >> 21) << 11) | ((r.z >> 21) << 22);
+            cls = classify_slot<COM, REFIT>(r, level, kids == 0, pre, nX, nY, nZ, rpack, f, f32, b32, rc2, th2);
+        }
+        top = top + 64 < kWaveBuf ? top + 64 : kWaveBuf;
+        const bool item = cls == 1 || cls == 2;
+        const uint64_t mi = __ballot(item);
+        if (cls != 3) kids = 0;
+        const int incl = wave_scan(kids);
+        const int push = __builtin_amdgcn_readlane(incl, 63), found = __popcll(mi);
+        if (ni + found > kWaveItems || ni + found + push > top) {
+            if (lane == 0) {
+                cnt[g] = icnt[g] = 0;
+                atomicAdd(&totals[3], 1ull);
+            }
+            return;
+        }
+        __syncthreads();   // the stack's entries are read before they are overwritten
+        if (item) buf[ni + __popcll(mi & lt)] = 2 * pre + (cls == 1 ? 1 : 0);
+        if (cls == 1) ++nc;
+        if (cls == 2) np += a;
+        ni += found;
+        top -= push;
+        int32_t* d = buf + top + incl - kids;
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+            if (k < kids) d[k] = (int32_t)a + k;
+        __syncthreads();
+    }
+    int32_t* out = items + g * kSlot;
+    if (ni <= 256) write_sorted<4>(buf, ni, lane, out);
+    else if (ni <= 512) write_sorted<8>(buf, ni, lane, out);
+    else if (ni <= 1024) write_sorted<16>(buf, ni, lane, out);
+    else write_sorted<32>(buf, ni, lane, out);
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) {
+        np += __shfl_xor(np, o, 64);
+        nc += __shfl_xor(nc, o, 64);
+    }
+    if (lane == 0) {
+        cnt[g] = (int64_t)np + nc;
+        icnt[g] = ni;
+        atomicAdd(&totals[0], (unsigned long long)np);
+        atomicAdd(&totals[1], (unsigned long long)nc);
+        atomicAdd(&totals[2], (unsigned long long)gcount[g] * ((unsigned long long)np + nc));
     }
 }
 
@@ -551,8 +778,7 @@ void build_lists(const Tree& t, Lists& l, hipStream_t st) {
     l.off.alloc(ng + 1, st);
     DevBuf<int64_t> icnt(ng + 1, st);
     DevBuf<int32_t> slots(ng * kSlot > 0 ? ng * kSlot : 1, st);
-    DevBuf<unsigned long long> totals(4, st);
-    fill_u64(totals.get(), 0ull, 4, st);
+    DevBuf<unsigned long long> totals(4 * kTotals, st);
     const int B = kListThreads;
     constexpr int G = kGroupsPerThread;
     const int64_t nthreads = (ng + G - 1) / G;
@@ -576,12 +802,36 @@ void build_lists(const Tree& t, Lists& l, hipStream_t st) {
             else walk(k_lists<G, W, false, false>, cnt, ic, tot, ioff, out);
         }
     };
-    walk_all(std::false_type{}, l.off.get(), icnt.get(), totals.get(), (const int64_t*)nullptr, slots.get());
-    SRF_HIP(hipGetLastError());
-    exclusive_scan_i64(l.off.get(), ng, true, st);
+    auto wave_walk = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)ng), dim3(64), 0, st, ng, t.glo.get(), t.ghi.get(), t.gcount.get(),
+                           t.srec.get(), t.spre.get(), t.nX.get(), t.nY.get(), t.nZ.get(), t.rpack.get(), rc2, th2,
+                           l.off.get(), icnt.get(), totals.get(), slots.get());
+    };
+    // sizes and items: by waves, and by threads when the tree is past the
+    // waves' range or some group's list does not fit a wave's buffer
+    std::vector<unsigned long long> rows(4 * kTotals);
     unsigned long long h[4];
-    SRF_HIP(hipMemcpyAsync(h, totals.get(), 4 * sizeof(unsigned long long), hipMemcpyDeviceToHost, st));
-    SRF_HIP(hipStreamSynchronize(st));
+    auto count = [&](bool waves) {
+        fill_u64(totals.get(), 0ull, 4 * kTotals, st);
+        if (!waves)
+            walk_all(std::false_type{}, l.off.get(), icnt.get(), totals.get(), (const int64_t*)nullptr, slots.get());
+        else if (t.refit)
+            com ? wave_walk(k_walk<true, true>) : wave_walk(k_walk<false, true>);
+        else
+            com ? wave_walk(k_walk<true, false>) : wave_walk(k_walk<false, false>);
+        SRF_HIP(hipGetLastError());
+        exclusive_scan_i64(l.off.get(), ng, true, st);
+        SRF_HIP(hipMemcpyAsync(rows.data(), totals.get(), rows.size() * sizeof(unsigned long long),
+                               hipMemcpyDeviceToHost, st));
+        SRF_HIP(hipStreamSynchronize(st));
+        for (int k = 0; k < 4; ++k) {
+            h[k] = 0;
+            for (int r = 0; r < kTotals; ++r) h[k] += rows[4 * r + k];
+        }
+    };
+    const bool waves = ng > 0 && t.srec.get();
+    count(waves);
+    if (waves && h[3] != 0) count(false);
     l.n_particle_entries = (int64_t)h[0];
     l.n_node_entries = (int64_t)h[1];
     l.n_entries = (int64_t)(h[0] + h[1]);

@@ -450,12 +450,27 @@ __global__ __launch_bounds__(kLvThreads) void k_cells(int64_t n, int64_t nblocks
     }
 }
 
+// The walk records of a cell (see common.h).
+__device__ __forceinline__ uint2 walk_record(const NodeGeo& g, int32_t count, int32_t skip) {
+    const uint32_t lv = g.level_leaf & 0xffu;
+    const uint32_t leaf = (g.level_leaf >> 8) & 1u;
+    const uint32_t oct = ((g.ix & 1u) << 2) | ((g.iy & 1u) << 1) | (g.iz & 1u);
+    const uint32_t cnt = count < (int32_t)kWalkCountMax ? (uint32_t)count : kWalkCountMax;
+    return make_uint2(lv | (leaf << 5) | (oct << 6) | (cnt << 9), (uint32_t)skip);
+}
+
+__device__ __forceinline__ uint4 slot_record(const NodeGeo& g, uint32_t a, int kids) {
+    return make_uint4(g.ix | ((a & 0x7ffu) << 21), g.iy | (((a >> 11) & 0x7ffu) << 21),
+                      g.iz | (((a >> 22) & 0x3ffu) << 21), (g.level_leaf & 0xffu) | ((uint32_t)kids << 5));
+}
+
 // One level, deepest first, 4 lanes per cell.  A leaf's particles run to
 // the first particle of the next cell in preorder; an inner cell's children
 // are the next level's slots from its first child on, while their first
 // particle lies before the first particle of the next slot of this level.
 // Sums and counts are kept per slot; count, skip link and monopole go to
-// the cell's preorder record, and the children get their parent.
+// the cell's preorder record, the children get their parent, and the cell
+// its two walk records.
 constexpr int kMomLanes = 4;
 
 __global__ __launch_bounds__(256) void k_moments(int32_t lo, int32_t hi, int32_t next_hi, int64_t n, int64_t nn,
@@ -469,7 +484,9 @@ __global__ __launch_bounds__(256) void k_moments(int32_t lo, int32_t hi, int32_t
                                                  double* __restrict__ sY, double* __restrict__ sZ,
                                                  NodeRange* __restrict__ rng, double* __restrict__ oM,
                                                  double* __restrict__ oX, double* __restrict__ oY,
-                                                 double* __restrict__ oZ, int32_t* __restrict__ leaf_of) {
+                                                 double* __restrict__ oZ, int32_t* __restrict__ leaf_of,
+                                                 const NodeGeo* __restrict__ geo, uint2* __restrict__ pack,
+                                                 uint4* __restrict__ srec) {
     const int64_t i = lo + blockIdx.x * (int64_t)(256 / kMomLanes) + threadIdx.x / kMomLanes;
     const int j = threadIdx.x & (kMomLanes - 1);
     const bool on = i < hi;
@@ -477,6 +494,7 @@ __global__ __launch_bounds__(256) void k_moments(int32_t lo, int32_t hi, int32_t
     const int32_t f = sfirst[c], pre = spre[c], ch = schild[c];
     double sm = 0, sx = 0, sy = 0, sz = 0;
     int64_t cnt = 0;
+    int kids = 0;
     if (on) {
         if (ch < 0) {
             const int64_t e = pre + 1 < nn ? pfirst[pre + 1] : n;
@@ -497,6 +515,7 @@ __global__ __launch_bounds__(256) void k_moments(int32_t lo, int32_t hi, int32_t
                 sy += sY[q];
                 sz += sZ[q];
                 cnt += scount[q];
+                ++kids;
                 rng[spre[q]].parent = pre;
             }
         }
@@ -508,6 +527,7 @@ __global__ __launch_bounds__(256) void k_moments(int32_t lo, int32_t hi, int32_t
         sy += __shfl_xor(sy, o, kMomLanes);
         sz += __shfl_xor(sz, o, kMomLanes);
         cnt += __shfl_xor(cnt, o, kMomLanes);
+        kids += __shfl_xor(kids, o, kMomLanes);
     }
     if (on && j == 0) {
         scount[c] = (int32_t)cnt;
@@ -518,7 +538,11 @@ __global__ __launch_bounds__(256) void k_moments(int32_t lo, int32_t hi, int32_t
         const int64_t e = f + cnt;
         rng[pre].first = f;
         rng[pre].count = (int32_t)cnt;
-        rng[pre].skip = e < n ? start[e] : (int32_t)nn;
+        const int32_t skip = e < n ? start[e] : (int32_t)nn;
+        rng[pre].skip = skip;
+        const NodeGeo g = geo[pre];
+        pack[pre] = walk_record(g, (int32_t)cnt, skip);
+        if (srec) srec[c] = slot_record(g, ch < 0 ? (uint32_t)cnt : (uint32_t)ch, kids);
         if (pre == 0) rng[pre].parent = -1;
         oM[pre] = sm;
         oX[pre] = sx / sm;
@@ -637,20 +661,6 @@ __device__ __forceinline__ uint4 pack16(const NodeGeo& g, const NodeRange& r) {
     pk.z = g.iz | (((sk >> 22) & 0x3ffu) << 21);
     pk.w = lv | (leaf ? 0x20u : 0u) | ((uint32_t)(r.count < (int32_t)kPackCountMax ? r.count : (int32_t)kPackCountMax) << 6);
     return pk;
-}
-
-// The 8-byte walk record of each cell (preorder).
-__global__ void k_pack(int64_t nn, const NodeGeo* __restrict__ geo, const NodeRange* __restrict__ rng,
-                       uint2* __restrict__ pack) {
-    const int64_t c = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (c >= nn) return;
-    const NodeGeo g = geo[c];
-    const NodeRange r = rng[c];
-    const uint32_t lv = g.level_leaf & 0xffu;
-    const uint32_t leaf = (g.level_leaf >> 8) & 1u;
-    const uint32_t oct = ((g.ix & 1u) << 2) | ((g.iy & 1u) << 1) | (g.iz & 1u);
-    const uint32_t cnt = r.count < (int32_t)kWalkCountMax ? (uint32_t)r.count : kWalkCountMax;
-    pack[c] = make_uint2(lv | (leaf << 5) | (oct << 6) | (cnt << 9), (uint32_t)r.skip);
 }
 
 // The walk record of each cell of a refitted tree (preorder): the packed
@@ -805,6 +815,7 @@ bool build_cells_and_groups(Tree& t, int32_t* d_flag, hipStream_t st) {
     t.sfirst.alloc(nn, st);
     t.spre.alloc(nn, st);
     t.schild.alloc(nn, st);
+    if (ng <= kWaveWalkGroups && nn < kWaveWalkCells) t.srec.alloc(nn, st);
     for (int L = 0; L <= kLevels; ++L) t.level_off[L] = base.off[L];
     int32_t* sfirst = t.sfirst.get();
     int32_t* spre = t.spre.get();
@@ -828,12 +839,10 @@ bool build_cells_and_groups(Tree& t, int32_t* d_flag, hipStream_t st) {
         hipLaunchKernelGGL(k_moments, dim3(grid_for(hi - lo, 256 / kMomLanes, 1 << 30)), dim3(256), 0, st, lo, hi,
                            next_hi, n, nn, sfirst, spre, schild, pfirst.get(), start.get(),
                            t.px.get(), t.py.get(), t.pz.get(), t.pm.get(), scount.get(), sM.get(), sX.get(), sY.get(),
-                           sZ.get(), t.range.get(), t.nM.get(), t.nX.get(), t.nY.get(), t.nZ.get(), t.leaf_of.get());
+                           sZ.get(), t.range.get(), t.nM.get(), t.nX.get(), t.nY.get(), t.nZ.get(), t.leaf_of.get(),
+                           t.geo.get(), t.pack.get(), t.srec.get());
         SRF_HIP(hipGetLastError());
     }
-    hipLaunchKernelGGL(k_pack, dim3(grid_for(nn, B, 1 << 30)), dim3(B), 0, st, nn, t.geo.get(), t.range.get(),
-                       t.pack.get());
-    SRF_HIP(hipGetLastError());
 
     // groups (from the marks and the sorted positions alone) on the second
     // stream, beside the cells (queued after them: the cells are the longer
