@@ -206,13 +206,13 @@ struct Src {
 
 // Load one list entry (particle v >= 0, or cell -v-1 as its monopole) as
 // the FP32 offset x_j - c - rint(x_j - c) from the group centre c, with its
-// mass, and classify it: far when its distance to the group's box (half
-// extents h) is at least r_cut/2, so that xi >= 1 holds for every target of
-// the group.  The distance is the FP64 distance from the source point
-// (particle or centre of mass) to the box.
+// mass, and the squared FP64 distance d2 from the source point (particle or
+// centre of mass) to the group's box (half extents h).  The entry is far
+// when that is at least r_cut/2, so that xi >= 1 holds for every target of
+// the group.
 template <class T, class V4>
-__device__ __forceinline__ V4 load_entry_cls(int32_t v, const Src& s, double cx, double cy, double cz, double hx,
-                                             double hy, double hz, double far2, bool& far) {
+__device__ __forceinline__ V4 load_entry_d2(int32_t v, const Src& s, double cx, double cy, double cz, double hx,
+                                            double hy, double hz, double& d2) {
     double X, Y, Z, M;
     if (v >= 0) {
         X = s.px[v];
@@ -231,7 +231,7 @@ __device__ __forceinline__ V4 load_entry_cls(int32_t v, const Src& s, double cx,
     ry -= rint(ry);
     rz -= rint(rz);
     const double ex = fmax(fabs(rx) - hx, 0.0), ey = fmax(fabs(ry) - hy, 0.0), ez = fmax(fabs(rz) - hz, 0.0);
-    far = ex * ex + ey * ey + ez * ez >= far2;
+    d2 = ex * ex + ey * ey + ez * ez;
     V4 o;
     o.x = (T)rx;
     o.y = (T)ry;
@@ -269,7 +269,9 @@ __device__ __forceinline__ int stage_tile(const int32_t* __restrict__ ent, int l
         int32_t v = 0;
         if (valid) {
             v = ent[k];
-            e = load_entry_cls<T, V4>(v, src, cx, cy, cz, hx, hy, hz, far2, far);
+            double d2;
+            e = load_entry_d2<T, V4>(v, src, cx, cy, cz, hx, hy, hz, d2);
+            far = d2 >= far2;
         }
         const uint64_t mn = __ballot(valid && !far), mf = __ballot(valid && far);
         if (valid) {
@@ -662,10 +664,124 @@ struct Targets {
     int32_t id[NB];     // sorted particle index, for the self test
 };
 
-// Entry blocks [a, b) of a staged tile (all near or all far).  Slots past
-// b hold entries of the next segment or the zero padding: their mass is
-// taken as zero, and their j-side sums are not added (the segment that owns
-// them adds its own).
+// A tile is staged with its near entries in slots [0, n_near) in list order
+// and its far entries in blocks of four ending at slot kAdjSlots.  A far
+// entry whose distance from the group's box is past r_cut is dropped: its
+// every pair is exactly zero (see drop_d2).  The k-th far entry of the tile,
+// dropped ones counted, belongs to class k mod 4; a class's entries stay on
+// one row of lanes and in order, last first, so that the sums a row forms do
+// not depend on what was dropped; the blocks are filled from the end, and a
+// class with fewer entries than another has empty slots (zero mass, row -1)
+// at the front.
+//
+// The four entries of a far block are usually neighbours (a leaf's
+// particles), and the group's targets in blocks of 16 are neighbours too, so
+// each block carries a mask of the target blocks that some entry of it can
+// reach; the others, whose pairs are all exactly zero, are skipped.
+// (The skipped pairs leave the far pairs one after another, each behind its
+// branch, instead of interleaved; four waves a SIMD hide that: taking the
+// target blocks two at a time was slower, 26.0 against 24.8 ms.)
+// Dropped entries and masks, adjoint kernel at r_cut of 6 spacings: 25.8 ->
+// 24.8 ms on the 2^24 lattice (15% of the far entries dropped, 11% of the far
+// blocks' targets skipped; without the masks 26.5 ms), 2.93 -> 2.42 ms on the
+// 2^20 clustered set (a quarter and a third).
+constexpr int kAdjSlots = kTile + kRows;
+
+// Squared distance from the group's box past which an entry's every pair is
+// exactly zero in the FP32 kernels, whose T = 1 - r k / 2 is clamped at 0:
+// offsets rounded to FP32 move r by at most 2^-24 times the box size and r
+// itself, and r's own arithmetic is good to a few 2^-24.
+__device__ __forceinline__ double drop_d2(double far2, double hx, double hy, double hz) {
+    const double d = (2.0 * sqrt(far2) + 1e-6 * (hx + hy + hz)) * (1.0 + 4e-6);
+    return d * d;
+}
+
+struct Staged {
+    int n_near;    // near entries
+    int blocks;    // far blocks
+    int slot0;     // 3 minus the class of lane row 0; row r's slot in a far block is (slot0 + r) & 3
+};
+
+// Stages one tile (see above).  `sub` holds the NB target blocks' boxes as
+// offsets from the group centre (centre xyz, half xyz, in FP32) and cut32
+// their squared reach; each far slot's bits go to `smask`.
+template <class T, class V4, int NB>
+__device__ __forceinline__ Staged stage_adjoint(const int32_t* __restrict__ ent, int len, int lane, const Src& src,
+                                                double cx, double cy, double cz, double hx, double hy, double hz,
+                                                double far2, double drop2, V4* tile, int32_t* ids, uint8_t* smask,
+                                                const float4* sub, float cut32, int32_t n_part) {
+    const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+    int nnear = 0, nfar = 0;
+    uint32_t kept = 0;   // far entries kept so far, 8 bits per class (a tile has at most 64 of a class)
+    for (int k0 = 0; k0 < len; k0 += 64) {
+        const int k = k0 + lane;
+        const bool valid = k < len;
+        bool far = false;
+        double d2 = 0.0;
+        V4 e;
+        int32_t v = 0;
+        if (valid) {
+            v = ent[k];
+            e = load_entry_d2<T, V4>(v, src, cx, cy, cz, hx, hy, hz, d2);
+            far = d2 >= far2;
+        }
+        const bool keep = valid && far && d2 < drop2;
+        const uint64_t mn = __ballot(valid && !far), mf = __ballot(valid && far);
+        const int cls = (nfar + __popcll(mf & lt)) & 3;
+        const uint32_t upto = kept + (uint32_t)wave_scan(keep ? 1 << (8 * cls) : 0);
+        const int rank = (int)((upto >> (8 * cls)) & 0xffu) - 1;   // where kept
+        kept = (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
+        const int pos = far ? kAdjSlots - 1 - (4 * rank + cls) : nnear + __popcll(mn & lt);
+        if (valid && (!far || keep)) {
+            tile[pos] = e;
+            ids[pos] = v >= 0 ? v : n_part + (-v - 1);
+        }
+        if (keep) {
+            uint32_t bits = 0;
+#pragma unroll
+            for (int ib = 0; ib < NB; ++ib) {
+                const float4 b = sub[2 * ib], h = sub[2 * ib + 1];
+                const float ex = fmaxf(fabsf((float)e.x - b.x) - h.x, 0.0f);
+                const float ey = fmaxf(fabsf((float)e.y - b.y) - h.y, 0.0f);
+                const float ez = fmaxf(fabsf((float)e.z - b.z) - h.z, 0.0f);
+                if (ex * ex + ey * ey + ez * ez < cut32) bits |= 1u << ib;
+            }
+            smask[pos] = (uint8_t)bits;
+        }
+        nnear += __popcll(mn);
+        nfar += __popcll(mf);
+    }
+    int cls_n[kRows], most = 0;
+#pragma unroll
+    for (int q = 0; q < kRows; ++q) {
+        cls_n[q] = (int)((kept >> (8 * q)) & 0xffu);
+        most = cls_n[q] > most ? cls_n[q] : most;
+    }
+    // empty slots lie beyond every target's reach, so that they add zeros
+    V4 z;
+    z.x = z.y = z.z = T(2);
+    z.w = T(0);
+#pragma unroll
+    for (int q = 0; q < kRows; ++q)
+        for (int r = cls_n[q] + lane; r < most; r += 64) {
+            const int pos = kAdjSlots - 1 - (4 * r + q);
+            tile[pos] = z;
+            ids[pos] = -1;
+            smask[pos] = 0;
+        }
+    if (lane < kRows && nnear + lane < kAdjSlots - 4 * most) {
+        tile[nnear + lane] = z;
+        ids[nnear + lane] = -1;
+    }
+    // the far entry at place q from the front of all nfar is on row q mod 4,
+    // as if none were dropped: row r takes class (nfar - 1 - r) mod 4
+    return {nnear, most, (3 - (nfar - 1)) & 3};
+}
+
+// The near entries (NEAR: slots [0, b)) or the far blocks [b blocks up to
+// kAdjSlots, block i from the end with its target-block mask in lane i of
+// vmask] of a staged tile.  Slots past n_near hold far entries or empty
+// ones: their mass is taken as zero, and their j-side sums are not added.
 // Row sums through LDS: after each entry block a lane stores its four
 // partial sums in `part` ([block][value][row][16], each [row][16] group
 // followed by one padding word, so that both the stores of one value by the
@@ -689,23 +805,32 @@ __device__ __forceinline__ void lds_order() {
 }
 
 template <class T, class V4, int NB, bool NEAR, bool RS>
-__device__ __forceinline__ void adjoint_entries(int a, int b, const V4* tile, const int32_t* ids,
+__device__ __forceinline__ void adjoint_entries(int b, int vmask, int slot0, const V4* tile, const int32_t* ids,
                                                 double* __restrict__ gj, T* part, int lane, Targets<T, NB>& tg,
                                                 const AdjCoef<T>& c) {
     const int ra = lane & (kRow - 1), rb = lane >> 4;
-    int nblk = 0, eb0 = a;
+    const int blocks = NEAR ? (b + kRows - 1) / kRows : b;
+    const int base = NEAR ? 0 : kAdjSlots - kRows * b;
+    int nblk = 0, blk0 = 0;
     T* wp = part + rb * kPartRow + ra;
+    const V4* tp = tile + base + (NEAR ? rb : (slot0 + rb) & 3);
     // this lane's sum in the reduction: block, value, row
     const int sb = lane >> 4, sv = (lane >> 2) & 3, sr = lane & 3;
     const T* rp = part + sb * kPartBlock + sv * kPartValue + sr * kPartRow;
-    for (int eb = a; eb < b; eb += kRows) {
-        const int e = eb + rb;
-        V4 p = tile[e];
-        p.w = e < b ? p.w : T(0);
-        const int32_t v = NEAR ? ids[e] : 0;
-        T jx, jy, jz, jm;
+    const int se = base + kRows * sb + (NEAR ? sr : (slot0 + sr) & 3);
+    for (int blk = 0; blk < blocks; ++blk) {
+        V4 p = tp[kRows * blk];
+        int32_t v = 0;
+        if (NEAR) {
+            const int e = kRows * blk + rb;
+            p.w = e < b ? p.w : T(0);
+            v = ids[e];
+        }
+        const int mask = NEAR ? -1 : __builtin_amdgcn_readlane(vmask, blocks - 1 - blk);
+        T jx = T(0), jy = T(0), jz = T(0), jm = T(0);
 #pragma unroll
         for (int ib = 0; ib < NB; ++ib) {
+            if (!NEAR && !(mask & (1 << ib))) continue;
             const T dx = p.x - tg.x[ib], dy = p.y - tg.y[ib], dz = p.z - tg.z[ib];
             // the far path with r from s needs no unsoftened r^2: s^2 directly
             const bool direct = !NEAR && RS;
@@ -723,7 +848,7 @@ __device__ __forceinline__ void adjoint_entries(int a, int b, const V4* tile, co
             tg.By[ib] = fma_(ms, dy, tg.By[ib]);
             tg.Bz[ib] = fma_(ms, dz, tg.Bz[ib]);
             // j-side: V = phi w + s d and phi (d . w), summed over the targets
-            if (ib == 0) {
+            if (NEAR && ib == 0) {
                 jx = fma_(s, dx, phi * tg.wx[ib]);
                 jy = fma_(s, dy, phi * tg.wy[ib]);
                 jz = fma_(s, dz, phi * tg.wz[ib]);
@@ -741,32 +866,52 @@ __device__ __forceinline__ void adjoint_entries(int a, int b, const V4* tile, co
         w[2 * kPartValue] = jz;
         w[3 * kPartValue] = jm;
         ++nblk;
-        if (nblk == kGroupBlocks || eb + kRows >= b) {
+        if (nblk == kGroupBlocks || blk + 1 == blocks) {
             lds_order();
-            const int e = eb0 + kRows * sb + sr;
-            if (sb < nblk && e < b) {
+            const int e = se + kRows * blk0;
+            if (sb < nblk && (!NEAR || e < b)) {
                 T sum = rp[0];
 #pragma unroll
                 for (int q = 1; q < kRow; ++q) sum += rp[q];
                 const T val = sv == 3 ? sum : sum * tile[e].w;
-                if (val != T(0)) unsafeAtomicAdd(gj + (4 * (int64_t)ids[e] + sv), kGScale * (double)val);
+                const int32_t row = ids[e];
+                if (val != T(0) && (NEAR || row >= 0))
+                    unsafeAtomicAdd(gj + (4 * (int64_t)row + sv), kGScale * (double)val);
             }
             lds_order();
             nblk = 0;
-            eb0 = eb + kRows;
+            blk0 = blk + 1;
         }
     }
 }
 
-template <class T, int NB, bool RS>
+// LDS of one wave.
+template <class T>
+struct AdjShared {
+    T part[kGroupBlocks * kPartBlock];   // row partials of the j-side sums
+    typename Vec4<T>::type tile[kAdjSlots];
+    int32_t ids[kAdjSlots];
+    float4 sub[2 * kRows];               // the target blocks' boxes: centre, half sizes
+    alignas(4) uint8_t smask[kAdjSlots];
+};
+
+// Smallest and largest value over a row of 16 lanes.
+__device__ __forceinline__ float row_min(float x) {
+#pragma unroll
+    for (int o = 1; o < kRow; o <<= 1) x = fminf(x, __shfl_xor(x, o, 64));
+    return x;
+}
+
+template <class T, int NB, bool RS, int W>
 __device__ __forceinline__ void adjoint_group(const GroupArgs& ga, const Src& src, const AdjCoef<T>& c0,
                                               const double* __restrict__ wx, const double* __restrict__ wy,
                                               const double* __restrict__ wz, int64_t ws, const AdjOut& out,
-                                              int64_t g, int32_t first, int32_t cnt,
-                                              typename Vec4<T>::type* tile, int32_t* ids, T* part) {
+                                              int64_t g, int32_t first, int32_t cnt, AdjShared<T>* sh_all) {
     using V4 = typename Vec4<T>::type;
     const AdjCoef<T> c = pinned(c0);
-    const int lane = threadIdx.x;
+    const int lane = threadIdx.x & 63;
+    const int wave = W == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    AdjShared<T>& sh = sh_all[wave];
     const int ra = lane & (kRow - 1), rb = lane >> 4;
     const double cx = (ga.glo[g * 3 + 0] + ga.ghi[g * 3 + 0]) * 0.5;
     const double cy = (ga.glo[g * 3 + 1] + ga.ghi[g * 3 + 1]) * 0.5;
@@ -774,6 +919,8 @@ __device__ __forceinline__ void adjoint_group(const GroupArgs& ga, const Src& sr
     const double hx = (ga.ghi[g * 3 + 0] - ga.glo[g * 3 + 0]) * 0.5;
     const double hy = (ga.ghi[g * 3 + 1] - ga.glo[g * 3 + 1]) * 0.5;
     const double hz = (ga.ghi[g * 3 + 2] - ga.glo[g * 3 + 2]) * 0.5;
+    const double drop2 = drop_d2(c0.far2, hx, hy, hz);
+    const float cut32 = (float)(drop2 * (1.0 + 2e-5) + 1e-6 * (hx * hx + hy * hy + hz * hz));
     Targets<T, NB> tg;
 #pragma unroll
     for (int ib = 0; ib < NB; ++ib) {
@@ -788,20 +935,35 @@ __device__ __forceinline__ void adjoint_group(const GroupArgs& ga, const Src& sr
         tg.wy[ib] = on ? (T)wy[wi] : T(0);
         tg.wz[ib] = on ? (T)wz[wi] : T(0);
         tg.id[ib] = on ? first + i : INT32_MIN;   // INT32_MIN is no list value
+        // the block's box (targets past the group's last leave it out)
+        const float px = (float)tg.x[ib], py = (float)tg.y[ib], pz = (float)tg.z[ib];
+        const float lx = row_min(on ? px : INFINITY), ux = -row_min(on ? -px : INFINITY);
+        const float ly = row_min(on ? py : INFINITY), uy = -row_min(on ? -py : INFINITY);
+        const float lz = row_min(on ? pz : INFINITY), uz = -row_min(on ? -pz : INFINITY);
+        if (lane == 0) {
+            sh.sub[2 * ib] = make_float4(0.5f * (lx + ux), 0.5f * (ly + uy), 0.5f * (lz + uz), 0.0f);
+            sh.sub[2 * ib + 1] = make_float4(0.5f * (ux - lx), 0.5f * (uy - ly), 0.5f * (uz - lz), 0.0f);
+        }
     }
     // FP64 i-side total of target `lane` (block rb, slot ra), kept by that lane
     double gx = 0.0, gy = 0.0, gz = 0.0;
     const int64_t e0 = ga.off[g], e1 = ga.off[g + 1];
-    for (int64_t tb = e0; tb < e1; tb += kTile) {
+    for (int64_t tb = e0 + (int64_t)wave * kTile; tb < e1; tb += W * kTile) {
         const int len = (int)((e1 - tb) < kTile ? (e1 - tb) : kTile);
-        __syncthreads();
-        const int nnear = stage_tile<T, V4, kRows>(ga.ent + tb, len, src, cx, cy, cz, hx, hy, hz, c0.far2, tile, ids,
-                                                   (int32_t)out.n);
-        __syncthreads();
+        lds_order();
+        const Staged stg = stage_adjoint<T, V4, NB>(ga.ent + tb, len, lane, src, cx, cy, cz, hx, hy, hz, c0.far2,
+                                                    drop2, sh.tile, sh.ids, sh.smask, sh.sub, cut32, (int32_t)out.n);
+        lds_order();
+        // lane i: the target blocks that far block i (from the end) can reach
+        uint32_t vm = 0;
+        if (lane < stg.blocks) vm = *reinterpret_cast<const uint32_t*>(sh.smask + kAdjSlots - kRows * (lane + 1));
+        vm |= vm >> 16;
+        vm |= vm >> 8;
 #pragma unroll
         for (int ib = 0; ib < NB; ++ib) tg.A[ib] = tg.Bx[ib] = tg.By[ib] = tg.Bz[ib] = T(0);
-        adjoint_entries<T, V4, NB, true, RS>(0, nnear, tile, ids, out.gj, part, lane, tg, c);
-        adjoint_entries<T, V4, NB, false, RS>(nnear, len, tile, ids, out.gj, part, lane, tg, c);
+        adjoint_entries<T, V4, NB, true, RS>(stg.n_near, 0, 0, sh.tile, sh.ids, out.gj, sh.part, lane, tg, c);
+        adjoint_entries<T, V4, NB, false, RS>(stg.blocks, (int)vm, stg.slot0, sh.tile, sh.ids, out.gj, sh.part, lane,
+                                              tg, c);
         // FP32 tile partials of the four rows summed in FP64 (xor 16, xor 32)
 #pragma unroll
         for (int ib = 0; ib < NB; ++ib) {
@@ -821,6 +983,22 @@ __device__ __forceinline__ void adjoint_group(const GroupArgs& ga, const Src& sr
             }
         }
     }
+    if (W > 1) {   // the waves' totals, added in order
+        static_assert(sizeof(sh.part) >= 64 * 3 * sizeof(double) || W == 1, "the totals fit the partials' space");
+        double* red = reinterpret_cast<double*>(sh.part);
+        lds_order();
+        red[lane * 3 + 0] = gx;
+        red[lane * 3 + 1] = gy;
+        red[lane * 3 + 2] = gz;
+        __syncthreads();
+        if (wave != 0) return;
+        for (int w = 1; w < W; ++w) {
+            const double* r = reinterpret_cast<const double*>(sh_all[w].part) + lane * 3;
+            gx += r[0];
+            gy += r[1];
+            gz += r[2];
+        }
+    }
     if (lane < cnt) {
         out.gix[first + lane] = gx;
         out.giy[first + lane] = gy;
@@ -828,25 +1006,22 @@ __device__ __forceinline__ void adjoint_group(const GroupArgs& ga, const Src& sr
     }
 }
 
-template <class T, bool RS>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 1))) void k_adjoint(GroupArgs ga, Src src, AdjCoef<T> c, const double* __restrict__ wx,
-                                                const double* __restrict__ wy, const double* __restrict__ wz, int64_t ws,
-                                                AdjOut out) {
-    using V4 = typename Vec4<T>::type;
-    __shared__ V4 tile[kTile + kRows];
-    __shared__ int32_t ids[kTile + kRows];
-    __shared__ T part[kGroupBlocks * kPartBlock];   // row partials of the j-side sums
+template <class T, bool RS, int W>
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 1))) void k_adjoint(
+    GroupArgs ga, Src src, AdjCoef<T> c, const double* __restrict__ wx, const double* __restrict__ wy,
+    const double* __restrict__ wz, int64_t ws, AdjOut out) {
+    __shared__ AdjShared<T> sh[W];
     const int64_t g = xcd_block(blockIdx.x, gridDim.x);
     const int32_t first = ga.gfirst[g], cnt = ga.gcount[g];
     static_assert(kRow * kRows == 64, "one wave is kRows rows of kRow lanes");
     if (cnt > 48)
-        adjoint_group<T, 4, RS>(ga, src, c, wx, wy, wz, ws, out, g, first, cnt, tile, ids, part);
+        adjoint_group<T, 4, RS, W>(ga, src, c, wx, wy, wz, ws, out, g, first, cnt, sh);
     else if (cnt > 32)
-        adjoint_group<T, 3, RS>(ga, src, c, wx, wy, wz, ws, out, g, first, cnt, tile, ids, part);
+        adjoint_group<T, 3, RS, W>(ga, src, c, wx, wy, wz, ws, out, g, first, cnt, sh);
     else if (cnt > 16)
-        adjoint_group<T, 2, RS>(ga, src, c, wx, wy, wz, ws, out, g, first, cnt, tile, ids, part);
+        adjoint_group<T, 2, RS, W>(ga, src, c, wx, wy, wz, ws, out, g, first, cnt, sh);
     else
-        adjoint_group<T, 1, RS>(ga, src, c, wx, wy, wz, ws, out, g, first, cnt, tile, ids, part);
+        adjoint_group<T, 1, RS, W>(ga, src, c, wx, wy, wz, ws, out, g, first, cnt, sh);
 }
 
 // Node sources -> member particles.  For a cell c0 and its ancestors c
@@ -933,6 +1108,18 @@ Src src_args(const Tree& t) {
 
 }  // namespace
 
+// Waves per group: a group's tiles are dealt to W waves, whose FP64 totals
+// are added at the end.  A tree of few groups leaves SIMDs idle, or waiting
+// for its longest list, with one wave each; one of many fills the chip
+// either way, and waves of one block wait for each other at its end.  Adjoint
+// kernel with 1 / 4 / 8 waves, us (clustered sets unless said otherwise):
+//   240 groups 446 / 132 / 89,  1550 groups 601 / 283 / 272,
+//   3050 groups 1106 / 435 / 435,  6000 groups 1100 / 736 / 811,
+//   25000 groups 2440 / 2340 / 2790,  51000 groups 4839 / 4738 / 5809,
+//   65000 groups (lattice) 8120 / 8433 / 10070.
+constexpr int64_t kOneWaveGroups = 40000;
+constexpr int64_t kFourWaveGroups = 2500;
+
 // Far pairs of the FP32 kernels take r = s - eps^2/(2 s) (see far_r) when
 // y = (2 eps / r_cut)^2 <= 5e-4, i.e. when its relative error y^2/8 stays
 // below 3.2e-8, half an FP32 ulp.
@@ -1018,16 +1205,23 @@ static void adjoint_on(const Tree& t, const Lists& l, const srf_params& p, const
     double* sb = saz + nn;
     fill_f64(o.gj, 0.0, 4 * (n + nn), st);
     if (ev0) SRF_HIP(hipEventRecord(ev0, st));
-    if (p.precision == SRF_FP64) {
-        hipLaunchKernelGGL((k_adjoint<double, false>), dim3((unsigned)ng), dim3(64), 0, st, group_args(t, l),
-                           src_args(t), make_adj_coef<double>(p.r_cut, p.eps), wx, wy, wz, ws, o);
-    } else if (far_r_from_s(p)) {
-        hipLaunchKernelGGL((k_adjoint<float, true>), dim3((unsigned)ng), dim3(64), 0, st, group_args(t, l),
-                           src_args(t), make_adj_coef<float>(p.r_cut, p.eps), wx, wy, wz, ws, o);
-    } else {
-        hipLaunchKernelGGL((k_adjoint<float, false>), dim3((unsigned)ng), dim3(64), 0, st, group_args(t, l),
-                           src_args(t), make_adj_coef<float>(p.r_cut, p.eps), wx, wy, wz, ws, o);
-    }
+    auto run = [&](auto coef, auto kernel, int waves) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)ng), dim3(64 * waves), 0, st, group_args(t, l), src_args(t), coef,
+                           wx, wy, wz, ws, o);
+    };
+    auto of_waves = [&](auto coef, auto k1, auto k4, auto k8) {
+        if (ng >= kOneWaveGroups) run(coef, k1, 1);
+        else if (ng >= kFourWaveGroups) run(coef, k4, 4);
+        else run(coef, k8, 8);
+    };
+    const AdjCoef<float> cf = make_adj_coef<float>(p.r_cut, p.eps);
+    if (p.precision == SRF_FP64)
+        of_waves(make_adj_coef<double>(p.r_cut, p.eps), k_adjoint<double, false, 1>, k_adjoint<double, false, 4>,
+                 k_adjoint<double, false, 8>);
+    else if (far_r_from_s(p))
+        of_waves(cf, k_adjoint<float, true, 1>, k_adjoint<float, true, 4>, k_adjoint<float, true, 8>);
+    else
+        of_waves(cf, k_adjoint<float, false, 1>, k_adjoint<float, false, 4>, k_adjoint<float, false, 8>);
     SRF_HIP(hipGetLastError());
     if (ev1) SRF_HIP(hipEventRecord(ev1, st));
     hipLaunchKernelGGL(k_node_chain, dim3(grid_for(nn, 256, 1 << 30)), dim3(256), 0, st, nn, t.range.get(), t.nM.get(),
