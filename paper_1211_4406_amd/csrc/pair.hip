@@ -4,7 +4,8 @@
 // registers as offsets from the group centre c_g; the group's list is
 // streamed through LDS in tiles of kTile entries, each entry converted once
 // (in FP64) to the offset x_j - c_g - rint(x_j - c_g) and stored with its
-// mass.  With N_i particles in the group, the wave runs S = floor(64/N_i)
+// mass.  (In trees of few groups several waves share a group, each with
+// tiles, or chunks of them, of its own.)  With N_i particles in the group, the wave runs S = floor(64/N_i)
 // independent j-streams (lane = i + N_i * stream), whose FP64 partial sums
 // are added at the end.  Each staged tile is split into near entries (some
 // target may lie within r_cut/2 of them) and far entries (none can); far
@@ -24,6 +25,7 @@
 #include <cmath>
 #include <mutex>
 #include <string>
+#include <type_traits>
 
 #include "common.h"
 
@@ -240,82 +242,168 @@ __device__ __forceinline__ V4 load_entry_d2(int32_t v, const Src& s, double cx, 
     return o;
 }
 
-// Stage one tile of a group's list in LDS, near entries first (slots
-// [0, n_near)) and far entries after them (filled from the end).  Returns
-// n_near; the order within each class is fixed by the list, so the result
-// is deterministic.  An entry that is one of the group's own particles is
-// near.  `ids`, if given, receives each entry's row in the adjoint's
-// source array (particle s -> s, cell c -> n_part + c).  The PAD slots after
-// the last entry are set to zero mass at the origin (row -1), so that a
-// read past the end of a segment stays finite.
-template <class T, class V4, int PAD = 0>
-__device__ __forceinline__ int stage_tile(const int32_t* __restrict__ ent, int len, const Src& src, double cx,
-                                          double cy, double cz, double hx, double hy, double hz, double far2,
-                                          V4* tile, int32_t* ids, int32_t n_part = 0) {
-    const int lane = threadIdx.x;
-    if (PAD > 0 && lane < PAD) {
-        V4 z;
-        z.x = z.y = z.z = z.w = T(0);
-        tile[len + lane] = z;
-        if (ids) ids[len + lane] = -1;
-    }
-    const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    int nnear = 0, nfar = 0;
-    for (int k0 = 0; k0 < len; k0 += 64) {
-        const int k = k0 + lane;
-        const bool valid = k < len;
-        bool far = false;
-        V4 e;
-        int32_t v = 0;
-        if (valid) {
-            v = ent[k];
-            double d2;
-            e = load_entry_d2<T, V4>(v, src, cx, cy, cz, hx, hy, hz, d2);
-            far = d2 >= far2;
-        }
-        const uint64_t mn = __ballot(valid && !far), mf = __ballot(valid && far);
-        if (valid) {
-            const int pos = far ? len - 1 - (nfar + __popcll(mf & lt)) : nnear + __popcll(mn & lt);
-            tile[pos] = e;
-            if (ids) ids[pos] = v >= 0 ? v : n_part + (-v - 1);
-        }
-        nnear += __popcll(mn);
-        nfar += __popcll(mf);
-    }
-    return nnear;
+// Squared distance from the group's box past which an entry's every pair is
+// exactly zero in the FP32 kernels, whose T = 1 - r k / 2 is clamped at 0:
+// offsets rounded to FP32 move r by at most 2^-24 times the box size and r
+// itself, and r's own arithmetic is good to a few 2^-24.
+__device__ __forceinline__ double drop_d2(double far2, double hx, double hy, double hz) {
+    const double d = (2.0 * sqrt(far2) + 1e-6 * (hx + hy + hz)) * (1.0 + 4e-6);
+    return d * d;
 }
 
-// Pairs of this lane's stream with the entries [a, b) of a staged tile
-// (entries a + st, a + st + S, ...).  The unrolled loop takes U entries
-// per stream (8 for the shorter far pairs, 4 for near pairs) while all
-// streams have U left, so its trip count is the same for every lane.  The
-// FP32 partial sums are added to the FP64 totals every kFlush entries:
+__device__ __forceinline__ void lds_order() {
+    // one wave: its LDS operations complete in order; this keeps the
+    // compiler from moving them across
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// One wave's tile of a group's list in LDS, for the force and the potential:
+// the near entries in list order, then the far ones, last first.  The FP32
+// partial sums are added to the FP64 totals every kFlush entries of a stream:
 // the rounding error of an FP32 running sum grows with its length, and on
 // near-uniform sets, where a particle's force is a small residual of its
 // neighbours' pulls, partials over a whole tile (256 entries) dominated the
-// error; chunks of 32 cost no measurable time.
+// error; chunks of 32 cost no measurable time.  With DROP (one stream) the
+// far entries that reach no target of the group are left out: their pairs
+// are exactly zero, and the chunks are those of the whole tile, so that the
+// sums are the same (force kernel 13.1 -> 12.8 ms on the 2^24 lattice, where
+// 15% of the far entries go, and 10.7 -> 9.8 ms on the 1.3e7 clustered set);
+// far_n[c] is the number of entries left in chunk c, and the entries past the last whole round of U of the unrolled loop, which form
+// a sum of their own, are chunk kTail.
 constexpr int kFlush = 32;
+constexpr int kTail = kTile / kFlush;
+
+template <class V4>
+struct TileShared {
+    V4 tile[kTile];
+    int32_t far_n[kTail + 1];
+};
+
+struct TileCount {
+    int near, all;   // near entries, and all entries staged
+};
+
+template <class T, class V4, bool DROP, int U>
+__device__ __forceinline__ TileCount stage_tile(const int32_t* __restrict__ ent, int len, int lane, const Src& src,
+                                                double cx, double cy, double cz, double hx, double hy, double hz,
+                                                double far2, double drop2, TileShared<V4>& sh, int32_t* ids,
+                                                int32_t n_part) {
+    constexpr int kSub = kTile / 64;
+    const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+    if (DROP && lane <= kTail) sh.far_n[lane] = 0;
+    V4 e[kSub];
+    int32_t id[kSub], kf[kSub], kr[kSub];   // row; place among the far entries, and among those kept (-1: near or dropped)
+    int nnear = 0, nfar = 0, nkept = 0;
+#pragma unroll
+    for (int j = 0; j < kSub; ++j) {
+        const int k = 64 * j + lane;
+        const bool valid = k < len;
+        kr[j] = -1;
+        kf[j] = 0;
+        bool far = false, keep = false;
+        if (valid) {
+            const int32_t v = ent[k];
+            double d2;
+            e[j] = load_entry_d2<T, V4>(v, src, cx, cy, cz, hx, hy, hz, d2);
+            if (ids) id[j] = v >= 0 ? v : n_part + (-v - 1);
+            far = d2 >= far2;
+            keep = far && (!DROP || d2 < drop2);
+        }
+        const uint64_t mn = __ballot(valid && !far), mf = __ballot(far), mk = DROP ? __ballot(keep) : mf;
+        if (valid && !far) {
+            const int pos = nnear + __popcll(mn & lt);
+            sh.tile[pos] = e[j];
+            if (ids) ids[pos] = id[j];
+        }
+        if (keep) {
+            kf[j] = nfar + __popcll(mf & lt);
+            kr[j] = nkept + __popcll(mk & lt);
+        }
+        nnear += __popcll(mn);
+        nfar += __popcll(mf);
+        nkept += __popcll(mk);
+    }
+    const int all = nnear + nkept, whole = nfar / U * U;
+#pragma unroll
+    for (int j = 0; j < kSub; ++j) {
+        if (kr[j] < 0) continue;
+        const int pos = all - 1 - kr[j];
+        sh.tile[pos] = e[j];
+        if (ids) ids[pos] = id[j];
+        if (DROP) {
+            const int q = nfar - 1 - kf[j];
+            atomicAdd(&sh.far_n[q < whole ? q / kFlush : kTail], 1);
+        }
+    }
+    return {nnear, all};
+}
+
+// Pairs of this lane's stream with the entries [a, b) of a staged tile
+// (entries a + st, a + st + S, ...), those of the chunks sub, sub + subs, ...
+// The unrolled loop takes U entries per stream (8 for the shorter far pairs, 4
+// for near pairs) while all streams have U left, so its trip count is the
+// same for every lane; the rest is a chunk of its own.
 template <class T, class V4, int S, bool NEAR, bool COMP, bool RS>
-__device__ __forceinline__ void force_segment(const V4* tile, int a, int b, int st, T xi, T yi, T zi,
-                                              const Coef<T>& c, double& sx, double& sy, double& sz) {
+__device__ __forceinline__ void force_segment(const V4* tile, int a, int b, int st, int sub, int subs, T xi, T yi,
+                                              T zi, const Coef<T>& c, double& sx, double& sy, double& sz) {
     constexpr int U = NEAR ? 4 : 8;
     constexpr int FL = kFlush / U;
-    const V4* tp = tile + a + st;
-    int kk = a;
-    while (kk + U * S <= b) {
+    const int rounds = (b - a) / (U * S), chunks = (rounds + FL - 1) / FL;
+    int u = sub;
+    for (; u < chunks; u += subs) {
+        const int r1 = (u + 1) * FL < rounds ? (u + 1) * FL : rounds;
+        const V4* tp = tile + a + st + u * FL * U * S;
         Acc<T, COMP> acc;
-        for (int it = 0; it < FL && kk + U * S <= b; ++it, kk += U * S, tp += U * S) {
+        for (int r = u * FL; r < r1; ++r, tp += U * S) {
             V4 pp[U];
 #pragma unroll
-            for (int u = 0; u < U; ++u) pp[u] = tp[u * S];
+            for (int q = 0; q < U; ++q) pp[q] = tp[q * S];
 #pragma unroll
-            for (int u = 0; u < U; ++u) pair_force<T, V4, NEAR, COMP, RS>(pp[u], xi, yi, zi, c, acc);
+            for (int q = 0; q < U; ++q) pair_force<T, V4, NEAR, COMP, RS>(pp[q], xi, yi, zi, c, acc);
         }
         acc.flush(sx, sy, sz);
     }
+    if (u != chunks) return;
     Acc<T, COMP> acc;
-    for (int k = kk + st; k < b; k += S, tp += S) pair_force<T, V4, NEAR, COMP, RS>(tp[0], xi, yi, zi, c, acc);
+    for (int k = a + rounds * U * S + st; k < b; k += S)
+        pair_force<T, V4, NEAR, COMP, RS>(tile[k], xi, yi, zi, c, acc);
     acc.flush(sx, sy, sz);
+}
+
+// The far entries of a tile staged with DROP: chunk c's entries follow those
+// of the chunks before it.
+template <class T, class V4, bool COMP, bool RS>
+__device__ __forceinline__ void force_far_chunks(const TileShared<V4>& sh, int a, int lane, int sub, int subs, T xi,
+                                                 T yi, T zi, const Coef<T>& c, double& sx, double& sy, double& sz) {
+    const int n_c = lane <= kTail ? sh.far_n[lane] : 0;
+    const int end_c = a + wave_scan(n_c);
+    for (int u = sub; u <= kTail; u += subs) {
+        const int n = __builtin_amdgcn_readlane(n_c, u);
+        if (n == 0) continue;
+        const V4* tp = sh.tile + __builtin_amdgcn_readlane(end_c, u) - n;
+        Acc<T, COMP> acc;
+        int k = 0;
+        for (; k + 8 <= n; k += 8, tp += 8) {
+            V4 pp[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) pp[q] = tp[q];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) pair_force<T, V4, false, COMP, RS>(pp[q], xi, yi, zi, c, acc);
+        }
+        if (k + 4 <= n) {
+            V4 pp[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) pp[q] = tp[q];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) pair_force<T, V4, false, COMP, RS>(pp[q], xi, yi, zi, c, acc);
+            k += 4;
+            tp += 4;
+        }
+        for (; k < n; ++k, ++tp) pair_force<T, V4, false, COMP, RS>(tp[0], xi, yi, zi, c, acc);
+        acc.flush(sx, sy, sz);
+    }
 }
 
 struct GroupArgs {
@@ -326,15 +414,37 @@ struct GroupArgs {
     const int32_t* perm;
 };
 
+// A block of W waves takes one group.  The group's tiles are dealt to the
+// waves; a list of fewer than W tiles is dealt chunk by chunk instead, each
+// tile to W / tiles waves, which all stage it.  The waves' FP64 sums are
+// added in a fixed order at the end.
+struct Deal {
+    int64_t tile;      // first tile
+    int64_t step;      // tiles from one to the next
+    int sub, subs;     // chunks sub, sub + subs, ... of each
+};
+
+template <int W>
+__device__ __forceinline__ Deal deal_tiles(int64_t entries, int wave) {
+    if (W == 1) return {0, 1, 0, 1};
+    const int64_t tiles = (entries + kTile - 1) / kTile;
+    if (tiles >= W) return {wave, W, 0, 1};
+    const int subs = tiles > 0 ? W / (int)tiles : 1;
+    if (wave / subs >= tiles) return {tiles, W, 0, 1};   // no work for this wave
+    return {wave / subs, W, wave % subs, subs};
+}
+
 // ------------------------------------------------------------------ force
-template <class T, int S, bool COMP, bool RS>
+template <class T, int S, int W, bool COMP, bool RS>
 __device__ __forceinline__ void force_group(const GroupArgs& ga, const Src& src, const Coef<T>& c0, double G,
                                             double* __restrict__ ax, double* __restrict__ ay,
                                             double* __restrict__ az, int64_t os, int64_t g, int32_t first,
-                                            int32_t cnt, typename Vec4<T>::type* tile, double* red) {
+                                            int32_t cnt, TileShared<typename Vec4<T>::type>* sh_all, double* red) {
     using V4 = typename Vec4<T>::type;
     const Coef<T> c = pinned(c0);
-    const int lane = threadIdx.x;
+    const int lane = threadIdx.x & 63;
+    const int wave = W == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    TileShared<V4>& sh = sh_all[wave];
     const int il = lane % cnt, st = lane / cnt;
     const bool active = st < S;
     const double cx = (ga.glo[g * 3 + 0] + ga.ghi[g * 3 + 0]) * 0.5;
@@ -343,32 +453,44 @@ __device__ __forceinline__ void force_group(const GroupArgs& ga, const Src& src,
     const double hx = (ga.ghi[g * 3 + 0] - ga.glo[g * 3 + 0]) * 0.5;
     const double hy = (ga.ghi[g * 3 + 1] - ga.glo[g * 3 + 1]) * 0.5;
     const double hz = (ga.ghi[g * 3 + 2] - ga.glo[g * 3 + 2]) * 0.5;
+    const double drop2 = drop_d2(c0.far2, hx, hy, hz);
     const int32_t me = first + il;
     const T xi = (T)image(src.px[me] - cx), yi = (T)image(src.py[me] - cy), zi = (T)image(src.pz[me] - cz);
     double sx = 0, sy = 0, sz = 0;
     const int64_t e0 = ga.off[g], e1 = ga.off[g + 1];
-    for (int64_t tb = e0; tb < e1; tb += kTile) {
+    const Deal deal = deal_tiles<W>(e1 - e0, wave);
+    for (int64_t tb = e0 + deal.tile * kTile; tb < e1; tb += deal.step * kTile) {
         const int len = (int)((e1 - tb) < kTile ? (e1 - tb) : kTile);
-        __syncthreads();
-        const int nnear = stage_tile<T, V4>(ga.ent + tb, len, src, cx, cy, cz, hx, hy, hz, c0.far2, tile, nullptr);
-        __syncthreads();
+        lds_order();
+        const TileCount tc = stage_tile<T, V4, S == 1, 8>(ga.ent + tb, len, lane, src, cx, cy, cz, hx, hy, hz,
+                                                          c0.far2, drop2, sh, nullptr, 0);
+        lds_order();
         if (active) {
-            force_segment<T, V4, S, true, COMP, RS>(tile, 0, nnear, st, xi, yi, zi, c, sx, sy, sz);
-            force_segment<T, V4, S, false, COMP, RS>(tile, nnear, len, st, xi, yi, zi, c, sx, sy, sz);
+            force_segment<T, V4, S, true, COMP, RS>(sh.tile, 0, tc.near, st, deal.sub, deal.subs, xi, yi, zi, c, sx,
+                                                    sy, sz);
+            if (S > 1)
+                force_segment<T, V4, S, false, COMP, RS>(sh.tile, tc.near, tc.all, st, deal.sub, deal.subs, xi, yi,
+                                                         zi, c, sx, sy, sz);
         }
+        // (one stream: every lane takes part, the idle ones as copies of target il)
+        if (S == 1)
+            force_far_chunks<T, V4, COMP, RS>(sh, tc.near, lane, deal.sub, deal.subs, xi, yi, zi, c, sx, sy, sz);
     }
-    red[lane * 3 + 0] = sx;
-    red[lane * 3 + 1] = sy;
-    red[lane * 3 + 2] = sz;
+    double* mine = red + threadIdx.x * 3;
+    mine[0] = sx;
+    mine[1] = sy;
+    mine[2] = sz;
     __syncthreads();
-    if (lane < cnt) {
+    if (wave == 0 && lane < cnt) {
         double tx = 0, ty = 0, tz = 0;
+        for (int w = 0; w < W; ++w) {
 #pragma unroll
-        for (int q = 0; q < S; ++q) {
-            const int l = lane + q * cnt;
-            tx += red[l * 3 + 0];
-            ty += red[l * 3 + 1];
-            tz += red[l * 3 + 2];
+            for (int q = 0; q < S; ++q) {
+                const double* r = red + (64 * w + lane + q * cnt) * 3;
+                tx += r[0];
+                ty += r[1];
+                tz += r[2];
+            }
         }
         const int64_t o = (int64_t)ga.perm[me] * os;
         ax[o] = G * tx;
@@ -378,20 +500,19 @@ __device__ __forceinline__ void force_group(const GroupArgs& ga, const Src& src,
 }
 
 // Streams per group: the largest of 1, 2, 3, 4, 8 with S * N_i <= 64.
-template <class T, bool COMP, bool RS>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 1))) void k_force(
+template <class T, int W, bool COMP, bool RS>
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 1))) void k_force(
     GroupArgs ga, Src src, Coef<T> c, double G, double* __restrict__ ax, double* __restrict__ ay,
     double* __restrict__ az, int64_t os) {
-    using V4 = typename Vec4<T>::type;
-    __shared__ V4 tile[kTile];
-    __shared__ double red[64 * 3];
+    __shared__ TileShared<typename Vec4<T>::type> sh[W];
+    __shared__ double red[64 * W * 3];
     const int64_t g = xcd_block(blockIdx.x, gridDim.x);
     const int32_t first = ga.gfirst[g], cnt = ga.gcount[g];
-    if (cnt > 32) force_group<T, 1, COMP, RS>(ga, src, c, G, ax, ay, az, os, g, first, cnt, tile, red);
-    else if (cnt > 21) force_group<T, 2, COMP, RS>(ga, src, c, G, ax, ay, az, os, g, first, cnt, tile, red);
-    else if (cnt > 16) force_group<T, 3, COMP, RS>(ga, src, c, G, ax, ay, az, os, g, first, cnt, tile, red);
-    else if (cnt > 8) force_group<T, 4, COMP, RS>(ga, src, c, G, ax, ay, az, os, g, first, cnt, tile, red);
-    else force_group<T, 8, COMP, RS>(ga, src, c, G, ax, ay, az, os, g, first, cnt, tile, red);
+    if (cnt > 32) force_group<T, 1, W, COMP, RS>(ga, src, c, G, ax, ay, az, os, g, first, cnt, sh, red);
+    else if (cnt > 21) force_group<T, 2, W, COMP, RS>(ga, src, c, G, ax, ay, az, os, g, first, cnt, sh, red);
+    else if (cnt > 16) force_group<T, 3, W, COMP, RS>(ga, src, c, G, ax, ay, az, os, g, first, cnt, sh, red);
+    else if (cnt > 8) force_group<T, 4, W, COMP, RS>(ga, src, c, G, ax, ay, az, os, g, first, cnt, sh, red);
+    else force_group<T, 8, W, COMP, RS>(ga, src, c, G, ax, ay, az, os, g, first, cnt, sh, red);
 }
 
 // -------------------------------------------------------------- potential
@@ -466,14 +587,41 @@ __device__ __forceinline__ T pair_pot(const V4& p, T xi, T yi, T zi, const PotCo
     return p.w * q * rinv;
 }
 
-template <class T, int S, bool RS>
+// n sources from p on (with their rows in id), S apart, one FP32 sum.
+template <class T, class V4, bool NEAR, bool RS>
+__device__ __forceinline__ T potential_chunk(const V4* p, const int32_t* id, int n, int step, int32_t me, T xi, T yi,
+                                             T zi, const PotCoef<T>& c) {
+    constexpr int U = 4;
+    T acc = 0;
+    int k = 0;
+    for (; k + U <= n; k += U, p += U * step, id += U * step) {
+        V4 pp[U];
+        bool self[U];
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            pp[q] = p[q * step];
+            self[q] = NEAR && id[q * step] == me;
+        }
+#pragma unroll
+        for (int q = 0; q < U; ++q) acc += pair_pot<T, V4, NEAR, RS>(pp[q], xi, yi, zi, c, self[q]);
+    }
+    for (; k < n; ++k, p += step, id += step)
+        acc += pair_pot<T, V4, NEAR, RS>(p[0], xi, yi, zi, c, NEAR && id[0] == me);
+    return acc;
+}
+
+template <class T, int S, int W, bool RS>
 __device__ __forceinline__ void potential_group(const GroupArgs& ga, const Src& src, const PotCoef<T>& c0, double G,
                                                 double* __restrict__ phi, int64_t os, int32_t n_part, int64_t g,
-                                                int32_t first, int32_t cnt, typename Vec4<T>::type* tile,
-                                                int32_t* ids, double* red) {
+                                                int32_t first, int32_t cnt,
+                                                TileShared<typename Vec4<T>::type>* sh_all, int32_t* ids_all,
+                                                double* red) {
     using V4 = typename Vec4<T>::type;
     const PotCoef<T> c = pinned(c0);
-    const int lane = threadIdx.x;
+    const int lane = threadIdx.x & 63;
+    const int wave = W == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    TileShared<V4>& sh = sh_all[wave];
+    int32_t* ids = ids_all + wave * kTile;
     const int il = lane % cnt, st = lane / cnt;
     const bool active = st < S;
     const double cx = (ga.glo[g * 3 + 0] + ga.ghi[g * 3 + 0]) * 0.5;
@@ -482,58 +630,67 @@ __device__ __forceinline__ void potential_group(const GroupArgs& ga, const Src& 
     const double hx = (ga.ghi[g * 3 + 0] - ga.glo[g * 3 + 0]) * 0.5;
     const double hy = (ga.ghi[g * 3 + 1] - ga.glo[g * 3 + 1]) * 0.5;
     const double hz = (ga.ghi[g * 3 + 2] - ga.glo[g * 3 + 2]) * 0.5;
+    const double drop2 = drop_d2(c0.far2, hx, hy, hz);
     const int32_t me = first + il;
     const T xi = (T)image(src.px[me] - cx), yi = (T)image(src.py[me] - cy), zi = (T)image(src.pz[me] - cz);
     double sum = 0.0;
     const int64_t e0 = ga.off[g], e1 = ga.off[g + 1];
-    for (int64_t tb = e0; tb < e1; tb += kTile) {
+    const Deal deal = deal_tiles<W>(e1 - e0, wave);
+    for (int64_t tb = e0 + deal.tile * kTile; tb < e1; tb += deal.step * kTile) {
         const int len = (int)((e1 - tb) < kTile ? (e1 - tb) : kTile);
-        __syncthreads();
-        const int nnear = stage_tile<T, V4>(ga.ent + tb, len, src, cx, cy, cz, hx, hy, hz, c0.far2, tile, ids,
-                                            n_part);
-        __syncthreads();
-        if (active) {
-            // FP32 partials over at most kFlush entries of this lane, added in FP64
-            for (int k0 = st; k0 < nnear; k0 += kFlush * S) {
-                const int k1 = k0 + kFlush * S < nnear ? k0 + kFlush * S : nnear;
-                T acc = 0;
-                for (int k = k0; k < k1; k += S) acc += pair_pot<T, V4, true, RS>(tile[k], xi, yi, zi, c, ids[k] == me);
-                sum += (double)acc;
+        lds_order();
+        const TileCount tc = stage_tile<T, V4, S == 1, 1>(ga.ent + tb, len, lane, src, cx, cy, cz, hx, hy, hz,
+                                                          c0.far2, drop2, sh, ids, n_part);
+        lds_order();
+        // FP32 partials over at most kFlush entries of this lane, added in FP64
+        auto segment = [&](auto near, int a, int b) {
+            constexpr bool NEAR = decltype(near)::value;
+            for (int k = a + deal.sub * kFlush * S; k < b; k += deal.subs * kFlush * S) {
+                const int left = b - k - st, n = left <= 0 ? 0 : (left + S - 1) / S;
+                sum += (double)potential_chunk<T, V4, NEAR, RS>(sh.tile + k + st, ids + k + st,
+                                                               n < kFlush ? n : kFlush, S, me, xi, yi, zi, c);
             }
-            for (int k0 = nnear + st; k0 < len; k0 += kFlush * S) {
-                const int k1 = k0 + kFlush * S < len ? k0 + kFlush * S : len;
-                T acc = 0;
-                for (int k = k0; k < k1; k += S) acc += pair_pot<T, V4, false, RS>(tile[k], xi, yi, zi, c, false);
-                sum += (double)acc;
+        };
+        if (active) {
+            segment(std::true_type{}, 0, tc.near);
+            if (S > 1) segment(std::false_type{}, tc.near, tc.all);
+        }
+        if (S == 1) {
+            const int n_c = lane <= kTail ? sh.far_n[lane] : 0;
+            const int end_c = tc.near + wave_scan(n_c);
+            for (int u = deal.sub; u < kTail; u += deal.subs) {
+                const int n = __builtin_amdgcn_readlane(n_c, u), k = __builtin_amdgcn_readlane(end_c, u) - n;
+                sum += (double)potential_chunk<T, V4, false, RS>(sh.tile + k, ids + k, n, 1, me, xi, yi, zi, c);
             }
         }
     }
-    red[lane] = active ? sum : 0.0;
+    red[threadIdx.x] = active ? sum : 0.0;
     __syncthreads();
-    if (lane < cnt) {
+    if (wave == 0 && lane < cnt) {
         double tot = 0.0;
+        for (int w = 0; w < W; ++w) {
 #pragma unroll
-        for (int q = 0; q < S; ++q) tot += red[lane + q * cnt];
+            for (int q = 0; q < S; ++q) tot += red[64 * w + lane + q * cnt];
+        }
         phi[(int64_t)ga.perm[me] * os] = -G * tot;
     }
 }
 
 // Streams per group as in the force kernel.  `n_part` is the particle count
 // (the staged rows of cells start there, so that no cell matches a target).
-template <class T, bool RS>
-__global__ __launch_bounds__(64) void k_potential(GroupArgs ga, Src src, PotCoef<T> c, double G,
-                                                  double* __restrict__ phi, int64_t os, int32_t n_part) {
-    using V4 = typename Vec4<T>::type;
-    __shared__ V4 tile[kTile];
-    __shared__ int32_t ids[kTile];
-    __shared__ double red[64];
+template <class T, int W, bool RS>
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 1))) void k_potential(
+    GroupArgs ga, Src src, PotCoef<T> c, double G, double* __restrict__ phi, int64_t os, int32_t n_part) {
+    __shared__ TileShared<typename Vec4<T>::type> sh[W];
+    __shared__ int32_t ids[W * kTile];
+    __shared__ double red[64 * W];
     const int64_t g = xcd_block(blockIdx.x, gridDim.x);
     const int32_t first = ga.gfirst[g], cnt = ga.gcount[g];
-    if (cnt > 32) potential_group<T, 1, RS>(ga, src, c, G, phi, os, n_part, g, first, cnt, tile, ids, red);
-    else if (cnt > 21) potential_group<T, 2, RS>(ga, src, c, G, phi, os, n_part, g, first, cnt, tile, ids, red);
-    else if (cnt > 16) potential_group<T, 3, RS>(ga, src, c, G, phi, os, n_part, g, first, cnt, tile, ids, red);
-    else if (cnt > 8) potential_group<T, 4, RS>(ga, src, c, G, phi, os, n_part, g, first, cnt, tile, ids, red);
-    else potential_group<T, 8, RS>(ga, src, c, G, phi, os, n_part, g, first, cnt, tile, ids, red);
+    if (cnt > 32) potential_group<T, 1, W, RS>(ga, src, c, G, phi, os, n_part, g, first, cnt, sh, ids, red);
+    else if (cnt > 21) potential_group<T, 2, W, RS>(ga, src, c, G, phi, os, n_part, g, first, cnt, sh, ids, red);
+    else if (cnt > 16) potential_group<T, 3, W, RS>(ga, src, c, G, phi, os, n_part, g, first, cnt, sh, ids, red);
+    else if (cnt > 8) potential_group<T, 4, W, RS>(ga, src, c, G, phi, os, n_part, g, first, cnt, sh, ids, red);
+    else potential_group<T, 8, W, RS>(ga, src, c, G, phi, os, n_part, g, first, cnt, sh, ids, red);
 }
 
 // ---------------------------------------------------------------- adjoint
@@ -687,15 +844,6 @@ struct Targets {
 // 2^20 clustered set (a quarter and a third).
 constexpr int kAdjSlots = kTile + kRows;
 
-// Squared distance from the group's box past which an entry's every pair is
-// exactly zero in the FP32 kernels, whose T = 1 - r k / 2 is clamped at 0:
-// offsets rounded to FP32 move r by at most 2^-24 times the box size and r
-// itself, and r's own arithmetic is good to a few 2^-24.
-__device__ __forceinline__ double drop_d2(double far2, double hx, double hy, double hz) {
-    const double d = (2.0 * sqrt(far2) + 1e-6 * (hx + hy + hz)) * (1.0 + 4e-6);
-    return d * d;
-}
-
 struct Staged {
     int n_near;    // near entries
     int blocks;    // far blocks
@@ -795,14 +943,6 @@ constexpr int kGroupBlocks = 4;
 constexpr int kPartRow = kRow;                     // one row's 16 partials
 constexpr int kPartValue = kRows * kPartRow + 1;   // one value of a block: 4 rows + padding
 constexpr int kPartBlock = 4 * kPartValue;
-
-__device__ __forceinline__ void lds_order() {
-    // one wave: its LDS operations complete in order; this keeps the
-    // compiler from moving them across
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 
 template <class T, class V4, int NB, bool NEAR, bool RS>
 __device__ __forceinline__ void adjoint_entries(int b, int vmask, int slot0, const V4* tile, const int32_t* ids,
@@ -1108,17 +1248,21 @@ Src src_args(const Tree& t) {
 
 }  // namespace
 
-// Waves per group: a group's tiles are dealt to W waves, whose FP64 totals
-// are added at the end.  A tree of few groups leaves SIMDs idle, or waiting
-// for its longest list, with one wave each; one of many fills the chip
-// either way, and waves of one block wait for each other at its end.  Adjoint
-// kernel with 1 / 4 / 8 waves, us (clustered sets unless said otherwise):
-//   240 groups 446 / 132 / 89,  1550 groups 601 / 283 / 272,
-//   3050 groups 1106 / 435 / 435,  6000 groups 1100 / 736 / 811,
-//   25000 groups 2440 / 2340 / 2790,  51000 groups 4839 / 4738 / 5809,
-//   65000 groups (lattice) 8120 / 8433 / 10070.
-constexpr int64_t kOneWaveGroups = 40000;
-constexpr int64_t kFourWaveGroups = 2500;
+// Waves per group.  A tree of few groups leaves SIMDs idle, or waiting for
+// its longest list, with one wave each; one of many fills the chip either way,
+// and waves of one block wait for each other at its end.  Kernel times with 1
+// / 4 / 8 waves, us (clustered sets unless said otherwise):
+//   groups           force                adjoint
+//   240              218 / - / 42         446 / 132 / 89
+//   1550             290 / 137 / 137      601 / 283 / 272
+//   3050             516 / 234 / 218      1106 / 435 / 435
+//   4200 (lattice)   307 / 265 / 281      571 / 503 / 550
+//   25000            1468 / 1367 / 1533   2440 / 2340 / 2790
+//   51000            2523 / 2476 / 2883   4839 / 4738 / 5809
+//   65000 (lattice)  4212 / 4284 / 5074   8120 / 8433 / 10070
+//   316000           9841 / 11004 / 14024
+constexpr int64_t kOneWaveGroups = 55000;
+constexpr int64_t kFourWaveGroups = 3500;
 
 // Far pairs of the FP32 kernels take r = s - eps^2/(2 s) (see far_r) when
 // y = (2 eps / r_cut)^2 <= 5e-4, i.e. when its relative error y^2/8 stays
@@ -1128,47 +1272,48 @@ static bool far_r_from_s(const srf_params& p) {
     return y <= 5e-4;
 }
 
+// Calls f with the number of waves per group for ng groups.
+template <class F>
+static void with_waves(int64_t ng, F&& f) {
+    if (ng >= kOneWaveGroups) f(std::integral_constant<int, 1>{});
+    else if (ng >= kFourWaveGroups) f(std::integral_constant<int, 4>{});
+    else f(std::integral_constant<int, 8>{});
+}
+
 void launch_force(const Tree& t, const Lists& l, const srf_params& p, double* ax, double* ay, double* az, int64_t os,
                   hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
     const int64_t ng = t.n_groups;
     if (ev0) SRF_HIP(hipEventRecord(ev0, st));
-    if (p.precision == SRF_FP64) {
-        hipLaunchKernelGGL((k_force<double, false, false>), dim3((unsigned)ng), dim3(64), 0, st, group_args(t, l),
-                           src_args(t), make_coef<double>(p.r_cut, p.eps), p.G, ax, ay, az, os);
-    } else {
+    with_waves(ng, [&](auto waves) {
+        constexpr int W = decltype(waves)::value;
+        auto run = [&](auto coef, auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3((unsigned)ng), dim3(64 * W), 0, st, group_args(t, l), src_args(t), coef,
+                               p.G, ax, ay, az, os);
+        };
+        const Coef<float> cf = make_coef<float>(p.r_cut, p.eps);
         const bool rs = far_r_from_s(p);
-        const Coef<float> c = make_coef<float>(p.r_cut, p.eps);
-        const GroupArgs ga = group_args(t, l);
-        const Src sa = src_args(t);
-        if (p.compensated && rs)
-            hipLaunchKernelGGL((k_force<float, true, true>), dim3((unsigned)ng), dim3(64), 0, st, ga, sa, c, p.G, ax,
-                               ay, az, os);
-        else if (p.compensated)
-            hipLaunchKernelGGL((k_force<float, true, false>), dim3((unsigned)ng), dim3(64), 0, st, ga, sa, c, p.G, ax,
-                               ay, az, os);
-        else if (rs)
-            hipLaunchKernelGGL((k_force<float, false, true>), dim3((unsigned)ng), dim3(64), 0, st, ga, sa, c, p.G, ax,
-                               ay, az, os);
-        else
-            hipLaunchKernelGGL((k_force<float, false, false>), dim3((unsigned)ng), dim3(64), 0, st, ga, sa, c, p.G, ax,
-                               ay, az, os);
-    }
+        if (p.precision == SRF_FP64) run(make_coef<double>(p.r_cut, p.eps), k_force<double, W, false, false>);
+        else if (p.compensated && rs) run(cf, k_force<float, W, true, true>);
+        else if (p.compensated) run(cf, k_force<float, W, true, false>);
+        else if (rs) run(cf, k_force<float, W, false, true>);
+        else run(cf, k_force<float, W, false, false>);
+    });
     SRF_HIP(hipGetLastError());
     if (ev1) SRF_HIP(hipEventRecord(ev1, st));
 }
 
 void launch_potential(const Tree& t, const Lists& l, const srf_params& p, double* phi, int64_t os, hipStream_t st) {
     const int64_t ng = t.n_groups;
-    if (p.precision == SRF_FP64) {
-        hipLaunchKernelGGL((k_potential<double, false>), dim3((unsigned)ng), dim3(64), 0, st, group_args(t, l),
-                           src_args(t), make_pot_coef<double>(p.r_cut, p.eps), p.G, phi, os, (int32_t)t.n);
-    } else if (far_r_from_s(p)) {
-        hipLaunchKernelGGL((k_potential<float, true>), dim3((unsigned)ng), dim3(64), 0, st, group_args(t, l),
-                           src_args(t), make_pot_coef<float>(p.r_cut, p.eps), p.G, phi, os, (int32_t)t.n);
-    } else {
-        hipLaunchKernelGGL((k_potential<float, false>), dim3((unsigned)ng), dim3(64), 0, st, group_args(t, l),
-                           src_args(t), make_pot_coef<float>(p.r_cut, p.eps), p.G, phi, os, (int32_t)t.n);
-    }
+    with_waves(ng, [&](auto waves) {
+        constexpr int W = decltype(waves)::value;
+        auto run = [&](auto coef, auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3((unsigned)ng), dim3(64 * W), 0, st, group_args(t, l), src_args(t), coef,
+                               p.G, phi, os, (int32_t)t.n);
+        };
+        if (p.precision == SRF_FP64) run(make_pot_coef<double>(p.r_cut, p.eps), k_potential<double, W, false>);
+        else if (far_r_from_s(p)) run(make_pot_coef<float>(p.r_cut, p.eps), k_potential<float, W, true>);
+        else run(make_pot_coef<float>(p.r_cut, p.eps), k_potential<float, W, false>);
+    });
     SRF_HIP(hipGetLastError());
 }
 
@@ -1205,23 +1350,16 @@ static void adjoint_on(const Tree& t, const Lists& l, const srf_params& p, const
     double* sb = saz + nn;
     fill_f64(o.gj, 0.0, 4 * (n + nn), st);
     if (ev0) SRF_HIP(hipEventRecord(ev0, st));
-    auto run = [&](auto coef, auto kernel, int waves) {
-        hipLaunchKernelGGL(kernel, dim3((unsigned)ng), dim3(64 * waves), 0, st, group_args(t, l), src_args(t), coef,
-                           wx, wy, wz, ws, o);
-    };
-    auto of_waves = [&](auto coef, auto k1, auto k4, auto k8) {
-        if (ng >= kOneWaveGroups) run(coef, k1, 1);
-        else if (ng >= kFourWaveGroups) run(coef, k4, 4);
-        else run(coef, k8, 8);
-    };
-    const AdjCoef<float> cf = make_adj_coef<float>(p.r_cut, p.eps);
-    if (p.precision == SRF_FP64)
-        of_waves(make_adj_coef<double>(p.r_cut, p.eps), k_adjoint<double, false, 1>, k_adjoint<double, false, 4>,
-                 k_adjoint<double, false, 8>);
-    else if (far_r_from_s(p))
-        of_waves(cf, k_adjoint<float, true, 1>, k_adjoint<float, true, 4>, k_adjoint<float, true, 8>);
-    else
-        of_waves(cf, k_adjoint<float, false, 1>, k_adjoint<float, false, 4>, k_adjoint<float, false, 8>);
+    with_waves(ng, [&](auto waves) {
+        constexpr int W = decltype(waves)::value;
+        auto run = [&](auto coef, auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3((unsigned)ng), dim3(64 * W), 0, st, group_args(t, l), src_args(t), coef,
+                               wx, wy, wz, ws, o);
+        };
+        if (p.precision == SRF_FP64) run(make_adj_coef<double>(p.r_cut, p.eps), k_adjoint<double, false, W>);
+        else if (far_r_from_s(p)) run(make_adj_coef<float>(p.r_cut, p.eps), k_adjoint<float, true, W>);
+        else run(make_adj_coef<float>(p.r_cut, p.eps), k_adjoint<float, false, W>);
+    });
     SRF_HIP(hipGetLastError());
     if (ev1) SRF_HIP(hipEventRecord(ev1, st));
     hipLaunchKernelGGL(k_node_chain, dim3(grid_for(nn, 256, 1 << 30)), dim3(256), 0, st, nn, t.range.get(), t.nM.get(),
