@@ -79,7 +79,7 @@ QCoef<T> make_qcoef(double rc, double eps) {
 }
 
 __device__ __forceinline__ float q_rsqrt(float x) { return __builtin_amdgcn_rsqf(x); }
-__device__ __forceinline__ double q_rsqrt(double x) { return 1.0 / sqrt(x); }
+__device__ __forceinline__ double q_rsqrt(double x) { return rsqrt64(x); }
 __device__ __forceinline__ float q_sat(float x) { return fminf(fmaxf(x, 0.0f), 1.0f); }
 __device__ __forceinline__ double q_sat(double x) { return fmin(fmax(x, 0.0), 1.0); }
 
