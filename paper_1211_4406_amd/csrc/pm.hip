@@ -93,11 +93,16 @@ __device__ __forceinline__ MeshBox wave_box(int64_t s0, int64_t s1, const double
     return b;
 }
 
-// The piece from part `part` on: returns its end and its box.
+// The piece from part `part` on: returns its end and its box (one of more
+// than `most` points where the parts do not fit).
 __device__ __forceinline__ int next_piece(const MeshBox* parts, int part, int n_parts, int reach, int most,
                                           MeshBox& box) {
     box = parts[part];
     int end = part + 1;
+    if (box.points(reach) > most) {   // too large by itself: with the parts after it that are, too
+        while (end < n_parts && parts[end].points(reach) > most) ++end;
+        return end;
+    }
     for (; end < n_parts; ++end) {
         MeshBox u;
 #pragma unroll
@@ -133,30 +138,34 @@ __device__ __forceinline__ int next_piece(const MeshBox* parts, int part, int n_
 // takes 0.1 ms; the rest is the runs' sums, one LDS atomic a lane each.
 constexpr int kAssignWaves = 8;
 constexpr int kAssignThreads = 64 * kAssignWaves;
+// Particles per workgroup: kChunk, halved down to 64 a wave while that leaves
+// fewer than kBlocks workgroups (50653 particles on 32^3: the call 215 us with
+// 4096 a workgroup, 106 us with 512).
 constexpr int kChunk = 4096;
-constexpr int kPart = kChunk / kAssignWaves;
+constexpr int kBlocks = 512;
 constexpr int kBoxMax = 3328;   // FP64 values in LDS (two workgroups per CU)
 constexpr int kWtRow = 68;      // 64 particles, padded: a block's reads fall on distinct banks
 
 __global__ __launch_bounds__(kAssignThreads) void k_tsc_assign(int64_t np, const double* __restrict__ px,
                                                                const double* __restrict__ py,
                                                                const double* __restrict__ pz,
-                                                               const double* __restrict__ pm, int n,
-                                                               double* __restrict__ mesh) {
+                                                               const double* __restrict__ pm, int n, int chunk,
+                                                               int most, double* __restrict__ mesh) {
     __shared__ double sum_at[kBoxMax];
     __shared__ MeshBox parts[kAssignWaves];
     __shared__ double wts[kAssignWaves][3][4][kWtRow];   // per wave: axis (x times the mass), point, particle
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int64_t c0 = (int64_t)blockIdx.x * kChunk, c1 = c0 + kChunk < np ? c0 + kChunk : np;
+    const int64_t c0 = (int64_t)blockIdx.x * chunk, c1 = c0 + chunk < np ? c0 + chunk : np;
+    const int per = chunk / kAssignWaves;   // particles per part
     const double q = (double)n * n * n;
     const int64_t nn = n;
-    const int64_t p0 = c0 + wave * kPart;
+    const int64_t p0 = c0 + wave * per;
     if (p0 < c1) {
-        const MeshBox b = wave_box(p0, p0 + kPart < c1 ? p0 + kPart : c1, px, py, pz, n, 0.0);
+        const MeshBox b = wave_box(p0, p0 + per < c1 ? p0 + per : c1, px, py, pz, n, 0.0);
         if (lane == 0) parts[wave] = b;
     }
-    const int n_parts = (int)((c1 - c0 + kPart - 1) / kPart);
+    const int n_parts = (int)((c1 - c0 + per - 1) / per);
     // this lane's place in the matrix blocks: depth, block, row or column
     const int kp = lane >> 4, ka = (lane >> 2) & 3, kb = lane & 3;
     const double* wx = wts[wave][0][ka] + kp;
@@ -165,13 +174,13 @@ __global__ __launch_bounds__(kAssignThreads) void k_tsc_assign(int64_t np, const
     __syncthreads();
     for (int part = 0; part < n_parts;) {
         MeshBox box;
-        const int end = next_piece(parts, part, n_parts, 4, kBoxMax, box);
-        const int64_t s0 = c0 + part * kPart;
-        const int cnt = (int)((c0 + end * kPart < c1 ? c0 + end * kPart : c1) - s0);
+        const int end = next_piece(parts, part, n_parts, 4, most, box);
+        const int64_t s0 = c0 + part * per;
+        const int cnt = (int)((c0 + end * per < c1 ? c0 + end * per : c1) - s0);
         part = end;
         const int bd1 = box.hi[1] - box.lo[1] + 4, bd2 = box.hi[2] - box.lo[2] + 4;
         const int64_t vol = box.points(4);
-        const bool boxed = vol <= kBoxMax;
+        const bool boxed = vol <= most;
         double* my_sum = sum_at + (ka * bd1 + kp) * bd2 + kb;
         if (boxed) {
             __syncthreads();   // the last piece's box has been read
@@ -449,34 +458,34 @@ __global__ void k_fd4(const double2* __restrict__ phi, int n, double4* __restric
 // whose rate bound the kernel: 0.96 -> 0.49 ms for 2^24 particles on 128^3
 // points, 125 -> 67 us for 2^21 on 64^3.
 constexpr int kInterpThreads = 256;
-constexpr int kInterp = 2048;
-constexpr int kInterpPart = kInterp / (kInterpThreads / 64);
+constexpr int kInterp = 2048;      // particles per workgroup, halved for few particles as the assignment's
 constexpr int kInterpBox = 1664;   // points: 39 KB of LDS, four workgroups per CU
 
 __global__ __launch_bounds__(kInterpThreads) void k_tsc_interp(int64_t np, const double* __restrict__ px,
                                                                const double* __restrict__ py,
                                                                const double* __restrict__ pz,
-                                                               const int32_t* __restrict__ perm, int n,
+                                                               const int32_t* __restrict__ perm, int n, int chunk,
                                                                const double4* __restrict__ acc,
                                                                double* __restrict__ ax, double* __restrict__ ay,
                                                                double* __restrict__ az, int64_t os) {
     __shared__ double fld[3][kInterpBox];
     __shared__ MeshBox parts[kInterpThreads / 64];
     const int tid = threadIdx.x, wave = tid >> 6;
-    const int64_t c0 = (int64_t)blockIdx.x * kInterp, c1 = c0 + kInterp < np ? c0 + kInterp : np;
+    const int64_t c0 = (int64_t)blockIdx.x * chunk, c1 = c0 + chunk < np ? c0 + chunk : np;
+    const int per = chunk / (kInterpThreads / 64);
     const int64_t nn = n;
-    const int64_t p0 = c0 + wave * kInterpPart;
+    const int64_t p0 = c0 + wave * per;
     if (p0 < c1) {
-        const MeshBox b = wave_box(p0, p0 + kInterpPart < c1 ? p0 + kInterpPart : c1, px, py, pz, n, 0.5);
+        const MeshBox b = wave_box(p0, p0 + per < c1 ? p0 + per : c1, px, py, pz, n, 0.5);
         if ((tid & 63) == 0) parts[wave] = b;
     }
-    const int n_parts = (int)((c1 - c0 + kInterpPart - 1) / kInterpPart);
+    const int n_parts = (int)((c1 - c0 + per - 1) / per);
     __syncthreads();
     for (int part = 0; part < n_parts;) {
         MeshBox box;
         const int end = next_piece(parts, part, n_parts, 3, kInterpBox, box);
-        const int64_t s0 = c0 + part * kInterpPart;
-        const int cnt = (int)((c0 + end * kInterpPart < c1 ? c0 + end * kInterpPart : c1) - s0);
+        const int64_t s0 = c0 + part * per;
+        const int cnt = (int)((c0 + end * per < c1 ? c0 + end * per : c1) - s0);
         part = end;
         const int bd1 = box.hi[1] - box.lo[1] + 3, bd2 = box.hi[2] - box.lo[2] + 3;
         const int64_t vol = box.points(3);
@@ -550,8 +559,16 @@ void launch_pm(const Tree& t, double G, double r_cut, int n, double* ax, double*
     double* density = reinterpret_cast<double*>(acc.get());   // until the first FFT pass has read it
     if (ev0) SRF_HIP(hipEventRecord(ev0, st));
     fill_f64(density, 0.0, cells, st);
-    hipLaunchKernelGGL(k_tsc_assign, dim3((unsigned)((np + kChunk - 1) / kChunk)), dim3(kAssignThreads), 0, st, np,
-                       t.px.get(), t.py.get(), t.pz.get(), t.pm.get(), n, density);
+    auto blocks = [&](int chunk) { return (unsigned)((np + chunk - 1) / chunk); };
+    int chunk = kChunk, ichunk = kInterp;
+    while (chunk > kAssignThreads && blocks(chunk) < kBlocks) chunk /= 2;
+    while (ichunk > kInterpThreads && blocks(ichunk) < 2 * kBlocks) ichunk /= 2;
+    // with fewer than a particle to two points a box has more points than its
+    // particles touch, and few particles fit one: no boxes then (30007
+    // particles on 64^3: the call 120 us, with boxes 210; on 16^3 68 and 70)
+    const int most = 2 * np < cells ? 0 : kBoxMax;
+    hipLaunchKernelGGL(k_tsc_assign, dim3(blocks(chunk)), dim3(kAssignThreads), 0, st, np, t.px.get(), t.py.get(),
+                       t.pz.get(), t.pm.get(), n, chunk, most, density);
     SRF_HIP(hipGetLastError());
     int log2n = 0;
     while ((1 << log2n) < n) ++log2n;
@@ -568,8 +585,8 @@ void launch_pm(const Tree& t, double G, double r_cut, int n, double* ax, double*
     pass(k_fft_axis<kInverse>, 2);
     hipLaunchKernelGGL(k_fd4, dim3(grid_for(cells, 256, 1 << 30)), dim3(256), 0, st, mesh.get(), n, acc.get());
     SRF_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_tsc_interp, dim3((unsigned)((np + kInterp - 1) / kInterp)), dim3(kInterpThreads), 0, st, np,
-                       t.px.get(), t.py.get(), t.pz.get(), t.perm.get(), n, acc.get(), ax, ay, az, os);
+    hipLaunchKernelGGL(k_tsc_interp, dim3(blocks(ichunk)), dim3(kInterpThreads), 0, st, np, t.px.get(), t.py.get(),
+                       t.pz.get(), t.perm.get(), n, ichunk, acc.get(), ax, ay, az, os);
     SRF_HIP(hipGetLastError());
     if (ev1) SRF_HIP(hipEventRecord(ev1, st));
 }
