@@ -41,7 +41,6 @@ constexpr int kLvThreads = 256;
 constexpr int kLvTile = 1024;                      // particles per block
 constexpr int kPer = kLvTile / kLvThreads;
 constexpr int kHalo = 64;                          // runs hold at most 65 particles
-constexpr int kLvSpan = kLvTile + 2 * kHalo;       // deltas of the range tables
 constexpr int kLvRuns = kLvTile + kHalo;           // run starts
 constexpr int kLog = 7;                            // range tables for lengths 1..64
 constexpr int kLeft = 512;                         // left reach of the sibling scans (7 siblings of <= 64, + 64)
@@ -66,6 +65,36 @@ __device__ __forceinline__ int64_t first_equal(const uint64_t* __restrict__ keys
     return lo;
 }
 
+// Whether the candidate of level lv >= 2 at index js of the deltas mn[0]
+// starts a group (see k_levels).  It holds at most n_group particles, so its
+// end is within reach; its left siblings before the closing one span at most 7
+// x 64 particles, inside the left reach.
+__device__ __forceinline__ bool starts_group(const int8_t (*mn)[kScanSpan], int js, int lv, int n_group) {
+    int end = js + 1;
+#pragma unroll
+    for (int k = kLog - 1; k >= 0; --k)
+        if (end + (1 << k) <= kScanSpan && mn[k][end] >= lv) end += 1 << k;
+    const int own = end - js;
+    uint64_t sizes = 0;   // the siblings' sizes, nearest first, 8 bits each
+    int ns = 0, pos = js;
+    while (ns < 7 && mn[0][pos] >= lv - 1) {   // pos is not the parent's first index
+        int at = pos;   // all deltas of [at, pos) are >= lv
+#pragma unroll
+        for (int k = kLog - 1; k >= 0; --k)
+            if (at >= (1 << k) && mn[k][at - (1 << k)] >= lv) at -= 1 << k;
+        const int c = pos - at + 1;   // the sibling starts at at - 1
+        if (at == 0 || c > n_group) break;
+        sizes |= (uint64_t)c << (8 * ns++);
+        pos -= c;
+    }
+    int run = 0;   // the run that is open before the candidate
+    for (int k = ns - 1; k >= 0; --k) {
+        const int c = (int)((sizes >> (8 * k)) & 0xffu);
+        run = run > 0 && run + c <= n_group ? run + c : c;
+    }
+    return !(run > 0 && run + own <= n_group);
+}
+
 // Per particle: delta, leaf level, the chain length of the cells starting
 // there and the group-start mark; per block and level the number of cells
 // (blk[L * nblocks + block]), and per block the sums of the chain lengths
@@ -75,71 +104,73 @@ __device__ __forceinline__ int64_t first_equal(const uint64_t* __restrict__ keys
 // the root or holding more than n_group) starts a group under the root, and
 // under any other parent unless the greedy run of the candidate siblings
 // before it (octant order, closed by a sibling with more than n_group
-// particles or by an overflow) takes it in.  Candidates under a parent of
-// level >= 1 are handled one at a time by the whole wave: the candidate's end
-// and its left siblings' starts are each the nearest index, among the 64
-// after (before) a position, with delta below the candidate's level; a
-// sibling whose start is further away holds more than n_group particles and
-// closes the run.
-__global__ __launch_bounds__(kLvThreads) void k_levels(int64_t n, const uint64_t* __restrict__ keys, int n_leaf,
+// particles or by an overflow) takes it in.  Under a parent of level >= 1 the
+// candidate's end and its left siblings' starts are each the nearest index
+// after (before) a position with delta below the candidate's level, found in
+// seven steps down the range table of minima; a sibling whose start is more
+// than n_group away closes the run.  Each lane looks up its own candidate:
+// with the wave scanning 64 deltas for one candidate after another this took
+// most of a tile's time (44 us at 4096 particles, now 31 with 256 threads and
+// 15 with 1024).
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void k_levels(int64_t n, const uint64_t* __restrict__ keys, int n_leaf,
                                                        int n_group, int64_t nblocks, int8_t* __restrict__ delta,
                                                        int8_t* __restrict__ leaflv, int32_t* __restrict__ chain,
                                                        int32_t* __restrict__ mark, int32_t* __restrict__ blk) {
-    __shared__ int8_t mn[kLog][kLvSpan];   // mn[k][j] = min delta over [j, j + 2^k)
+    constexpr int PER = kLvTile / THREADS;
+    __shared__ int8_t mn[kLog][kScanSpan]; // mn[k][j] = min delta over [j, j + 2^k), j from b0 - kLeft on
     __shared__ int8_t mx[kLog][kLvRuns];   // mx[k][j] = max run minimum over run starts [j, j + 2^k)
-    __shared__ int8_t dl[kScanSpan];       // delta of global index b0 - kLeft + j
+    const int8_t* dl = mn[0];              // the deltas themselves
     __shared__ unsigned lh[kLevels + 2];   // cells per level; the tile's chain and mark sums
     const int64_t b0 = blockIdx.x * (int64_t)kLvTile;
     const int tid = threadIdx.x, lane = tid & 63;
     if (tid < kLevels + 2) lh[tid] = 0;
-    for (int j = tid; j < kScanSpan; j += kLvThreads) {
+    for (int j = tid; j < kScanSpan; j += THREADS) {
         const int64_t i = b0 - kLeft + j;
         int d = -1;
         if (i >= 1 && i < n) d = shared_digits(keys[i - 1], keys[i]);
-        dl[j] = (int8_t)d;
+        mn[0][j] = (int8_t)d;
     }
-    __syncthreads();
-    // range table of minima over [b0 - kHalo, b0 + kLvTile + kHalo)
-    for (int j = tid; j < kLvSpan; j += kLvThreads) mn[0][j] = dl[j + kLeft - kHalo];
     __syncthreads();
     for (int k = 1; k < kLog; ++k) {
         const int h = 1 << (k - 1);
-        for (int j = tid; j < kLvSpan; j += kLvThreads) {
+        for (int j = tid; j < kScanSpan; j += THREADS) {
             // entries whose range runs past the span are never queried
-            const int a = mn[k - 1][j], b = j + h < kLvSpan ? mn[k - 1][j + h] : a;
+            const int a = mn[k - 1][j], b = j + h < kScanSpan ? mn[k - 1][j + h] : a;
             mn[k][j] = (int8_t)(a < b ? a : b);
         }
         __syncthreads();
     }
-    int lam[2][kPer];
+    int lam[2][PER];
 #pragma unroll
     for (int w = 0; w < 2; ++w) {
         const int W = (w == 0 ? n_leaf : n_group) + 1;   // run length, 2..65
         const int kq = floor_log2(W - 1);
         // minimum of delta over the interior of the run starting at each t
-        for (int j = tid; j < kLvRuns; j += kLvThreads) {
+        for (int j = tid; j < kLvRuns; j += THREADS) {
             const int64_t t = b0 - kHalo + j;
             int v = -1;
             if (t >= 0 && t + W - 1 <= n - 1) {
-                const int a = mn[kq][j + 1], b = mn[kq][j + W - (1 << kq)];
+                const int jm = j + kLeft - kHalo;
+                const int a = mn[kq][jm + 1], b = mn[kq][jm + W - (1 << kq)];
                 v = a < b ? a : b;
             }
             mx[0][j] = (int8_t)v;
         }
         __syncthreads();
-        for (int k = 1; k < kLog; ++k) {
+        const int kr = floor_log2(W);
+        for (int k = 1; k <= kr; ++k) {
             const int h = 1 << (k - 1);
-            for (int j = tid; j < kLvRuns; j += kLvThreads) {
+            for (int j = tid; j < kLvRuns; j += THREADS) {
                 const int a = mx[k - 1][j], b = j + h < kLvRuns ? mx[k - 1][j + h] : a;
                 mx[k][j] = (int8_t)(a > b ? a : b);
             }
             __syncthreads();
         }
         // maximum over the runs [s - W + 1, s] that contain s
-        const int kr = floor_log2(W);
 #pragma unroll
-        for (int q = 0; q < kPer; ++q) {
-            const int js = kHalo + tid + q * kLvThreads;
+        for (int q = 0; q < PER; ++q) {
+            const int js = kHalo + tid + q * THREADS;
             const int a = mx[kr][js - W + 1], b = mx[kr][js - (1 << kr) + 1];
             lam[w][q] = a > b ? a : b;
         }
@@ -147,17 +178,16 @@ __global__ __launch_bounds__(kLvThreads) void k_levels(int64_t n, const uint64_t
     }
     int32_t csum = 0, msum = 0;   // this thread's chain lengths and group marks
 #pragma unroll
-    for (int q = 0; q < kPer; ++q) {
-        const int64_t s = b0 + tid + q * kLvThreads;   // a wave holds 64 consecutive particles
+    for (int q = 0; q < PER; ++q) {
+        const int64_t s = b0 + tid + q * THREADS;   // a wave holds 64 consecutive particles
         const bool on = s < n;
-        const int js = kLeft + tid + q * kLvThreads;  // index of s in dl
+        const int js = kLeft + tid + q * THREADS;  // index of s in dl
         const int d = dl[js];
         int ll = lam[0][q] + 1;
         ll = ll < 1 ? 1 : (ll > kMaxLevel ? kMaxLevel : ll);
         const int lg = lam[1][q];
         const int kap = lg + 1 > 1 ? lg + 1 : 1;
         int m = 0;
-        bool walk = false;
         if (on) {
             delta[s] = (int8_t)d;
             leaflv[s] = (int8_t)ll;
@@ -167,49 +197,8 @@ __global__ __launch_bounds__(kLvThreads) void k_levels(int64_t n, const uint64_t
             if (lg >= kMaxLevel) {
                 m = ((s - first_equal(keys, 0, s)) % n_group) == 0;   // chunks of a level-21 cell
             } else if (d < kap) {
-                if (kap == 1) m = 1;
-                else walk = true;
+                m = kap == 1 || starts_group(mn, js, kap, n_group);
             }
-        }
-        // candidates under a parent of level >= 1, one per wave iteration
-        uint64_t todo = __ballot(walk);
-        while (todo) {
-            const int src = __ffsll((unsigned long long)todo) - 1;
-            todo &= todo - 1;
-            const int cs = __shfl(js, src, 64);
-            const int ck = __shfl(kap, src, 64);
-            const int64_t cg = __shfl(s, src, 64);
-            // the candidate's end: the first delta below its level among the
-            // next 64 (it holds at most n_group, so the end is among them)
-            const int de = cg + 1 + lane < n ? dl[cs + 1 + lane] : -1;
-            const uint64_t eb = __ballot(de < ck);
-            const int64_t own = __ffsll((unsigned long long)eb);
-            // left siblings back to the parent's start or a closing sibling;
-            // they span at most 7 x 64 particles, inside the left reach
-            int64_t cnt[7];
-            int ns = 0;
-            int pos = cs;
-            while (ns < 7 && dl[pos] >= ck - 1) {   // pos is not the parent's first index
-                const int jb = pos - 1 - lane;
-                const int db = jb >= 0 ? dl[jb] : -1;
-                const uint64_t bb = __ballot(db < ck);
-                if (!bb) break;   // no start within 64: the sibling holds more than n_group
-                const int c = __ffsll((unsigned long long)bb);
-                if (c > n_group) break;
-                cnt[ns++] = c;
-                pos -= c;
-            }
-            int64_t run = 0;
-            bool open = false;
-            for (int k = ns - 1; k >= 0; --k) {
-                if (open && run + cnt[k] <= n_group) {
-                    run += cnt[k];
-                } else {
-                    run = cnt[k];
-                    open = true;
-                }
-            }
-            if (lane == src) m = !(open && run + own <= n_group);
         }
         if (on) mark[s] = m;
         msum += on ? m : 0;
@@ -764,8 +753,16 @@ bool build_cells_and_groups(Tree& t, int32_t* d_flag, hipStream_t st) {
     DevBuf<int8_t> delta(n, st), leaflv(n, st);
     DevBuf<int32_t> start(n + 1, st), mark(n + 1, st), blk((kLevels + 2) * nblocks, st), tot(kLevels + 2, st);
     DevBuf<Summary> dsum(1, st);
-    hipLaunchKernelGGL(k_levels, dim3((unsigned)nblocks), dim3(kLvThreads), 0, st, n, t.keys.get(), t.n_leaf,
-                       t.n_group, nblocks, delta.get(), leaflv.get(), start.get(), mark.get(), blk.get());
+    auto levels = [&](auto kernel, int threads) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)nblocks), dim3(threads), 0, st, n, t.keys.get(), t.n_leaf, t.n_group,
+                           nblocks, delta.get(), leaflv.get(), start.get(), mark.get(), blk.get());
+    };
+    // a particle per thread where the tiles do not fill the chip (the kernel
+    // is then one tile's latency: 34 us with 256 threads, 14 with 1024, at
+    // 131071 particles); four where they do, beside the gather on the second
+    // stream (278 against 720 us at 1.3e7)
+    if (nblocks <= 512) levels(k_levels<1024>, 1024);
+    else levels(k_levels<256>, 256);
     SRF_HIP(hipGetLastError());
     hipLaunchKernelGGL(k_level_scan, dim3(kLevels + 2), dim3(256), 0, st, nblocks, blk.get(), tot.get());
     SRF_HIP(hipGetLastError());
