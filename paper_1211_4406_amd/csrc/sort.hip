@@ -12,6 +12,8 @@
 // word.  Both give the order of (key, input index), that of eight passes
 // over the whole 64-bit key.  The sorted keys are recomputed from the
 // sorted positions by the final gather.
+#include <utility>
+
 #include "common.h"
 
 namespace srf {
@@ -61,21 +63,23 @@ __global__ void k_keys(int64_t n, const double* __restrict__ x, const double* __
 }
 
 // ------------------------------------------------------------- radix sort
-// Eight LSD passes of 8 bits over the 64-bit key.  A block sorts a tile of
-// kTile keys; its wave w owns the kWaveKeys consecutive keys starting at
-// w * kWaveKeys, read in rounds of 64 (item r of lane l is key
-// w * kWaveKeys + 64 r + l), so a key's rank within its wave needs no
-// block-wide barrier.  Each pass: per-tile digit counts (k_hist), their
+// LSD passes of 8 bits.  A block sorts a tile of 256 ITEMS keys; its wave w
+// owns the 64 ITEMS consecutive keys starting at 64 ITEMS w, read in rounds of
+// 64 (item r of lane l is key 64 ITEMS w + 64 r + l), so a key's rank within
+// its wave needs no block-wide barrier.  Each pass: per-tile digit counts (k_hist), their
 // exclusive scan over the tiles of each digit (k_digit_scan), and the stable
-// scatter (k_scatter), which adds the scan over digits itself.
+// scatter (k_scatter), which adds the scan over digits itself.  With few tiles
+// (SELF) a scatter block adds up the counts of the tiles before its own itself,
+// from counts laid out tile by tile, and the scan's launch is saved.
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / 64;
 constexpr int kItems = 16;   // keys per thread: tiles of 4096 (8 and 12 measured no faster at 2^24)
-constexpr int kWaveKeys = 64 * kItems;
-constexpr int kTile = kThreads * kItems;  // keys per block
+constexpr int kFewItems = 4; // and for at most kFewKeys keys, where a tile's latency counts: tiles of 1024
+constexpr int64_t kFewKeys = 1 << 19;
 constexpr int kDigits = 256;
 static_assert(kThreads == kDigits, "one digit per thread in the per-digit steps");
 
+template <int ITEMS, bool SELF>
 __global__ __launch_bounds__(kThreads) void k_hist(int64_t n, const uint32_t* __restrict__ keys, int shift,
                                                    int64_t tiles, int32_t* __restrict__ counts) {
     __shared__ int32_t h[kWaves][kDigits];
@@ -83,21 +87,21 @@ __global__ __launch_bounds__(kThreads) void k_hist(int64_t n, const uint32_t* __
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) h[w][tid] = 0;
     __syncthreads();
-    const int64_t base = blockIdx.x * (int64_t)kTile + wid * kWaveKeys + lane;
-    uint32_t k[kItems];
+    const int64_t base = blockIdx.x * (int64_t)(kThreads * ITEMS) + wid * 64 * ITEMS + lane;
+    uint32_t k[ITEMS];
 #pragma unroll
-    for (int r = 0; r < kItems; ++r) {
+    for (int r = 0; r < ITEMS; ++r) {
         const int64_t i = base + 64 * r;
         k[r] = i < n ? keys[i] : 0u;
     }
 #pragma unroll
-    for (int r = 0; r < kItems; ++r)
+    for (int r = 0; r < ITEMS; ++r)
         if (base + 64 * r < n) atomicAdd(&h[wid][(k[r] >> shift) & 0xff], 1);
     __syncthreads();
     int32_t c = 0;
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) c += h[w][tid];
-    counts[(int64_t)tid * tiles + blockIdx.x] = c;
+    counts[SELF ? (int64_t)blockIdx.x * kDigits + tid : (int64_t)tid * tiles + blockIdx.x] = c;
 }
 
 // Exclusive scan of one digit's row of per-tile counts (block = digit), in
@@ -149,13 +153,14 @@ __global__ __launch_bounds__(kThreads) void k_digit_scan(int64_t tiles, int32_t*
 // plus the number of such lanes below it.  Tile position: digits in order,
 // within a digit the waves in order, then the rank.  The tile is reordered
 // in LDS so that each digit's run is written contiguously.
-template <bool V2>
+template <bool V2, int ITEMS, bool SELF>
 __global__ __launch_bounds__(kThreads) void k_scatter(int64_t n, const uint32_t* __restrict__ kin,
                                                       const int32_t* __restrict__ vin, uint32_t* __restrict__ kout,
                                                       int32_t* __restrict__ vout, const uint32_t* __restrict__ v2in,
                                                       uint32_t* __restrict__ v2out, int shift, int64_t tiles,
                                                       const int32_t* __restrict__ offsets,
                                                       const int32_t* __restrict__ dtot) {
+    constexpr int kTile = kThreads * ITEMS;
     __shared__ int32_t wc[kWaves][kDigits];   // running counts, then the waves' exclusive prefix
     __shared__ int32_t toff[kDigits];         // tile-local exclusive offset of each digit
     __shared__ int32_t gdst[kDigits];         // global position of the tile's first key of each digit
@@ -166,22 +171,32 @@ __global__ __launch_bounds__(kThreads) void k_scatter(int64_t n, const uint32_t*
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) wc[w][tid] = 0;
-    const int32_t tile_base = offsets[(int64_t)tid * tiles + blockIdx.x];
-    const int32_t digit_total = dtot[tid];
+    int32_t tile_base = 0, digit_total = 0;
+    if (SELF) {
+#pragma unroll 8
+        for (int64_t k = 0; k < tiles; ++k) {
+            const int32_t c = offsets[k * kDigits + tid];
+            tile_base += k < blockIdx.x ? c : 0;
+            digit_total += c;
+        }
+    } else {
+        tile_base = offsets[(int64_t)tid * tiles + blockIdx.x];
+        digit_total = dtot[tid];
+    }
     __syncthreads();
     const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    const int64_t wbase = blockIdx.x * (int64_t)kTile + wid * kWaveKeys + lane;
-    uint32_t key[kItems], val2[kItems];
-    int32_t val[kItems], rank[kItems];
+    const int64_t wbase = blockIdx.x * (int64_t)kTile + wid * 64 * ITEMS + lane;
+    uint32_t key[ITEMS], val2[ITEMS];
+    int32_t val[ITEMS], rank[ITEMS];
 #pragma unroll
-    for (int r = 0; r < kItems; ++r) {
+    for (int r = 0; r < ITEMS; ++r) {
         const int64_t i = wbase + 64 * r;
         key[r] = i < n ? kin[i] : 0u;
         val[r] = i < n ? vin[i] : 0;
         val2[r] = (V2 && i < n) ? v2in[i] : 0u;
     }
 #pragma unroll
-    for (int r = 0; r < kItems; ++r) {
+    for (int r = 0; r < ITEMS; ++r) {
         const bool valid = wbase + 64 * r < n;
         const int d = (int)((key[r] >> shift) & 0xff);
         // lanes holding the same digit (invalid lanes match only each other)
@@ -241,7 +256,7 @@ __global__ __launch_bounds__(kThreads) void k_scatter(int64_t n, const uint32_t*
     gdst[tid] = og + tile_base;
     __syncthreads();
 #pragma unroll
-    for (int r = 0; r < kItems; ++r) {
+    for (int r = 0; r < ITEMS; ++r) {
         if (wbase + 64 * r >= n) continue;
         const int d = (int)((key[r] >> shift) & 0xff);
         const int p = toff[d] + wc[wid][d] + rank[r];
@@ -255,7 +270,7 @@ __global__ __launch_bounds__(kThreads) void k_scatter(int64_t n, const uint32_t*
     const int64_t tbase = blockIdx.x * (int64_t)kTile;
     const int cnt = (int)((n - tbase) < kTile ? (n - tbase) : kTile);
 #pragma unroll
-    for (int r = 0; r < kItems; ++r) {
+    for (int r = 0; r < ITEMS; ++r) {
         const int p = r * kThreads + tid;
         if (p < cnt) {
             const uint32_t k = skey[p];
@@ -424,6 +439,60 @@ __global__ void k_sorted_keys(int64_t n, const int32_t* __restrict__ perm, const
     keys[s] = ((uint64_t)hi[s] << 32) | lo[perm[s]];
 }
 
+// For at most kFewKeys particles: what the run kernels, k_sorted_keys and
+// k_gather do, in one.  The high words are sorted, so a member of a run finds
+// the run's ends by bisection over the kRunMax positions either way, and its
+// rank by comparing itself with the run's members.  (Fourteen launches, each a
+// few us of latency, for what is a few us of work here; for many particles the
+// compacted runs are read faster.)  Whole forward pass, us, with the general
+// kernels / these and the small tiles: 4096 particles 365 / 295, 20001 500 /
+// 410, 131071 697 / 620, 262139 910 / 840, 524287 1252 / 1241, 10^6 2000 / 2098.
+__global__ void k_finish(int64_t n, const uint32_t* __restrict__ hi, const int32_t* __restrict__ idx,
+                         const uint32_t* __restrict__ klo, const double* __restrict__ x, const double* __restrict__ y,
+                         const double* __restrict__ z, int64_t ps, const double* __restrict__ m, int64_t ms,
+                         int32_t* __restrict__ perm, uint64_t* __restrict__ keys, double* __restrict__ px,
+                         double* __restrict__ py, double* __restrict__ pz, double* __restrict__ pm,
+                         int32_t* __restrict__ flag) {
+    const int64_t s = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (s >= n) return;
+    const int32_t id = idx[s];
+    const uint32_t h = hi[s], lo = klo[id];
+    const double a = x[id * ps], b = y[id * ps], c = z[id * ps], mm = m[id * ms];
+    int64_t at = s;
+    if (in_run(hi, n, s)) {
+        int64_t r0 = s > kRunMax ? s - kRunMax : 0, top = s;   // first position of h
+        while (r0 < top) {
+            const int64_t mid = (r0 + top) >> 1;
+            if (hi[mid] < h) r0 = mid + 1;
+            else top = mid;
+        }
+        int64_t r1 = s + 1, end = s + 1 + kRunMax < n ? s + 1 + kRunMax : n;   // one past its last
+        while (r1 < end) {
+            const int64_t mid = (r1 + end) >> 1;
+            if (hi[mid] <= h) r1 = mid + 1;
+            else end = mid;
+        }
+        if (r1 - r0 > kRunMax) {
+            atomicOr(flag, 8);   // the caller sorts again in full
+        } else {
+            int32_t rank = 0;
+#pragma unroll 4
+            for (int64_t k = r0; k < r1; ++k) {
+                const int32_t ik = idx[k];
+                const uint32_t lk = klo[ik];
+                rank += (lk < lo || (lk == lo && ik < id)) ? 1 : 0;
+            }
+            at = r0 + rank;
+        }
+    }
+    perm[at] = id;
+    keys[at] = ((uint64_t)h << 32) | lo;
+    px[at] = wrap01(a);
+    py[at] = wrap01(b);
+    pz[at] = wrap01(c);
+    pm[at] = mm;
+}
+
 // The same gather for a tree reused at new positions, with the input checks
 // of k_keys; without masses (m == nullptr) only the positions are gathered.
 __global__ void k_gather_checked(int64_t n, const int32_t* __restrict__ perm, const double* __restrict__ x,
@@ -467,24 +536,30 @@ void build_sorted(Tree& t, const double* x, const double* y, const double* z, in
     hipLaunchKernelGGL(k_keys, dim3(grid_for(n, B, 1 << 30)), dim3(B), 0, st, n, x, y, z, ps, m, ms, ka.get(),
                        ha.get(), t.perm.get(), d_flag);
     SRF_HIP(hipGetLastError());
-    const int64_t tiles = (n + kTile - 1) / kTile;
+    const bool few = !full && n <= kFewKeys;
+    const int64_t tile = kThreads * (few ? kFewItems : kItems);
+    const int64_t tiles = (n + tile - 1) / tile;
     DevBuf<int32_t> counts(kDigits * tiles, st);
     DevBuf<int32_t> dtot(kDigits, st);
     // one stable pass of 8 bits over the words k (with index v and, for the
     // low word, the high word h carried along)
     auto pass = [&](int shift, const uint32_t* k, uint32_t* k2, const int32_t* v, int32_t* v2, const uint32_t* h,
                     uint32_t* h2) {
-        hipLaunchKernelGGL(k_hist, dim3((unsigned)tiles), dim3(kThreads), 0, st, n, k, shift, tiles, counts.get());
-        SRF_HIP(hipGetLastError());
-        hipLaunchKernelGGL(k_digit_scan, dim3(kDigits), dim3(kThreads), 0, st, tiles, counts.get(), dtot.get());
-        SRF_HIP(hipGetLastError());
-        if (h)
-            hipLaunchKernelGGL(k_scatter<true>, dim3((unsigned)tiles), dim3(kThreads), 0, st, n, k, v, k2, v2, h, h2,
-                               shift, tiles, counts.get(), dtot.get());
-        else
-            hipLaunchKernelGGL(k_scatter<false>, dim3((unsigned)tiles), dim3(kThreads), 0, st, n, k, v, k2, v2,
-                               (const uint32_t*)nullptr, (uint32_t*)nullptr, shift, tiles, counts.get(), dtot.get());
-        SRF_HIP(hipGetLastError());
+        auto run = [&](auto hist, auto scatter, bool scan) {
+            hipLaunchKernelGGL(hist, dim3((unsigned)tiles), dim3(kThreads), 0, st, n, k, shift, tiles, counts.get());
+            SRF_HIP(hipGetLastError());
+            if (scan) {
+                hipLaunchKernelGGL(k_digit_scan, dim3(kDigits), dim3(kThreads), 0, st, tiles, counts.get(),
+                                   dtot.get());
+                SRF_HIP(hipGetLastError());
+            }
+            hipLaunchKernelGGL(scatter, dim3((unsigned)tiles), dim3(kThreads), 0, st, n, k, v, k2, v2, h, h2, shift,
+                               tiles, counts.get(), dtot.get());
+            SRF_HIP(hipGetLastError());
+        };
+        if (few) run(k_hist<kFewItems, true>, k_scatter<false, kFewItems, true>, false);
+        else if (h) run(k_hist<kItems, false>, k_scatter<true, kItems, false>, true);
+        else run(k_hist<kItems, false>, k_scatter<false, kItems, false>, true);
     };
     // full: the low word first, passes a -> b -> a -> b -> a (pairs of
     // passes return to the first buffers), then the high word, already in
@@ -498,6 +573,19 @@ void build_sorted(Tree& t, const double* x, const double* y, const double* z, in
     for (int p = 0; p < 4; p += 2) {
         pass(8 * p, ha.get(), hb.get(), t.perm.get(), vb.get(), nullptr, nullptr);
         pass(8 * (p + 1), hb.get(), ha.get(), vb.get(), t.perm.get(), nullptr, nullptr);
+    }
+    t.px.alloc(n, st);
+    t.py.alloc(n, st);
+    t.pz.alloc(n, st);
+    t.pm.alloc(n, st);
+    t.release_events();
+    if (few) {
+        hipLaunchKernelGGL(k_finish, dim3(grid_for(n, 64, 1 << 30)), dim3(64), 0, st, n, ha.get(), t.perm.get(),
+                           ka.get(), x, y, z, ps, m, ms, vb.get(), t.keys.get(), t.px.get(), t.py.get(), t.pz.get(),
+                           t.pm.get(), d_flag);
+        SRF_HIP(hipGetLastError());
+        t.perm = std::move(vb);
+        return;
     }
     if (!full) {
         const dim3 grid(grid_for(n, B, 1 << 30));
@@ -531,11 +619,6 @@ void build_sorted(Tree& t, const double* x, const double* y, const double* z, in
                            rstart.get(), t.perm.get(), d_flag);
         SRF_HIP(hipGetLastError());
     }
-    t.px.alloc(n, st);
-    t.py.alloc(n, st);
-    t.pz.alloc(n, st);
-    t.pm.alloc(n, st);
-    t.release_events();
     if (full) {
         hipLaunchKernelGGL(k_gather<true>, dim3(grid_for(n, B, 1 << 30)), dim3(B), 0, st, n, t.perm.get(), x, y, z,
                            ps, m, ms, t.px.get(), t.py.get(), t.pz.get(), t.pm.get(), t.keys.get());
