@@ -116,16 +116,17 @@ int srf_tree_build(int64_t n, const double* x, const double* y, const double* z,
         t.n_group = p->n_group;
         t.n_leaf = p->n_leaf;
         t.stream = st;
-        srf::DevBuf<int32_t> flag(1, st);
-        srf::fill_i32(flag.get(), 0, 1, st);
-        srf::build_sorted(t, x, y, z, pos_stride, m, m_stride, flag.get(), false, st);
+        srf::DevBuf<int32_t> stat(srf::kStatWords, st);
+        int32_t* flag = stat.get() + srf::kStatFlag;
+        srf::fill_i32(flag, 0, 1, st);
+        srf::build_sorted(t, x, y, z, pos_stride, m, m_stride, flag, false, st);
         // reads the flag at its one synchronisation (SRF_EDOMAIN); when more
         // particles than the run sort takes share one high key word (a dense
         // clump in a 2^-10 cube), the tree is built again on the full sort
-        if (!srf::build_cells_and_groups(t, flag.get(), st)) {
-            srf::fill_i32(flag.get(), 0, 1, st);
-            srf::build_sorted(t, x, y, z, pos_stride, m, m_stride, flag.get(), true, st);
-            if (!srf::build_cells_and_groups(t, flag.get(), st))
+        if (!srf::build_cells_and_groups(t, stat.get(), st)) {
+            srf::fill_i32(flag, 0, 1, st);
+            srf::build_sorted(t, x, y, z, pos_stride, m, m_stride, flag, true, st);
+            if (!srf::build_cells_and_groups(t, stat.get(), st))
                 srf::fail(SRF_EHIP, "the full radix sort reported an incomplete order");
         }
     });
@@ -149,15 +150,12 @@ int srf_tree_refit(srf_tree* t, const double* x, const double* y, const double* 
         // gather into new buffers: the tree is untouched until the inputs pass
         srf::DevBuf<double> nx(n, st), ny(n, st), nz(n, st), nm;
         if (m) nm.alloc(n, st);
-        srf::DevBuf<int32_t> flag(1, st);
-        srf::fill_i32(flag.get(), 0, 1, st);
-        srf::gather_refit(T, x, y, z, pos_stride, m, m_stride, flag.get(), nx.get(), ny.get(), nz.get(),
+        srf::HostSlot slot(st);
+        srf::gather_refit(T, x, y, z, pos_stride, m, m_stride, slot.device<int32_t>(2), nx.get(), ny.get(), nz.get(),
                           m ? nm.get() : nullptr, st);
-        int32_t hflag = 0;
-        SRF_HIP(hipMemcpyAsync(&hflag, flag.get(), sizeof(int32_t), hipMemcpyDeviceToHost, st));
-        SRF_HIP(hipStreamSynchronize(st));
-        if (hflag & 1) srf::fail(SRF_EDOMAIN, "non-finite particle position");
-        if (hflag & 2) srf::fail(SRF_EDOMAIN, "particle mass not finite and > 0");
+        const int32_t* bad = slot.wait<int32_t>();
+        if (bad[0]) srf::fail(SRF_EDOMAIN, "non-finite particle position");
+        if (bad[1]) srf::fail(SRF_EDOMAIN, "particle mass not finite and > 0");
         T.px = std::move(nx);
         T.py = std::move(ny);
         T.pz = std::move(nz);

@@ -37,6 +37,45 @@ void dev_release_all();
 // buffer it touches is allocated on the caller's stream.
 hipStream_t aux_stream();
 
+// A small piece of pinned host memory that kernels write and the host reads
+// after it has synchronised the stream: without the copy to pageable memory,
+// which is a kernel and two runtime calls of its own.  From a pool that holds
+// as many pieces as calls were ever in progress at once; srf_release_cache
+// returns them.  Given back only when no kernel can write it any more: the
+// destructor synchronises the stream if the call left it before doing so.
+constexpr size_t kHostSlotBytes = 256;
+void* host_slot_take();
+void host_slot_give(void* p);
+
+struct HostSlot {
+    void* p;
+    hipStream_t s;
+    explicit HostSlot(hipStream_t stream) : p(host_slot_take()), s(stream) {}
+    HostSlot(const HostSlot&) = delete;
+    HostSlot& operator=(const HostSlot&) = delete;
+    ~HostSlot() {
+        if (!read) (void)hipStreamSynchronize(s);
+        host_slot_give(p);
+    }
+    // synchronises the stream; the contents may then be read
+    template <class T>
+    const T* wait() {
+        check_hip(hipStreamSynchronize(s), "hipStreamSynchronize");
+        read = true;
+        return static_cast<const T*>(p);
+    }
+    // for kernels queued from here on to write; its first n values are zero
+    template <class T>
+    T* device(int n = 0) {
+        for (int i = 0; i < n; ++i) static_cast<T*>(p)[i] = T(0);
+        read = false;
+        return static_cast<T*>(p);
+    }
+
+private:
+    bool read = true;
+};
+
 template <class T>
 struct DevBuf {
     T* p = nullptr;
@@ -98,7 +137,11 @@ constexpr uint32_t kWalkCountMax = 0x7fffffu;
 //   x = ix | (a & 0x7ff) << 21,  y = iy | ((a >> 11) & 0x7ff) << 21,
 //   z = iz | ((a >> 22) & 0x3ff) << 21,  w = level | children << 5,
 // a = the slot of the first child, or a leaf's (children = 0) particle count.
-constexpr int64_t kWaveWalkGroups = 3 << 16;   // largest number of groups walked by waves (lists.hip)
+// Trees whose lists are built by one wave per group (lists.hip): those of at
+// most kWaveWalkGroups groups, and up to kDeepWalkGroups in a tree deeper than
+// a uniform set's by kDeepLevels.
+constexpr int64_t kWaveWalkGroups = 3 << 16, kDeepWalkGroups = 1 << 20;
+constexpr int kDeepLevels = 4;
 constexpr int64_t kWaveWalkCells = 1 << 30;    // and of cells (items are sorted as 31-bit keys)
 // A cell of a refitted tree for the list traversal, 32 bytes: the packed
 // record and its box rounded outward to multiples of q = 2^-(level + 10),
@@ -138,7 +181,7 @@ struct Tree {
     // particle; a cell's children are one run of the next level's slots):
     // first particle, preorder id and first child slot (-1 for a leaf)
     DevBuf<int32_t> sfirst, spre, schild;
-    DevBuf<uint4> srec;        // slot-ordered walk records (none past kWaveWalkGroups groups)
+    DevBuf<uint4> srec;        // slot-ordered walk records (where the waves' walk is taken)
     DevBuf<double> clo, chi;   // [nn*3] boxes of the cells of a refitted tree
     DevBuf<RefitCell> rpack;   // their walk records
     // groups, in order of first
@@ -234,6 +277,9 @@ void exclusive_scan_i64(int64_t* data, int64_t n, bool write_total, hipStream_t 
 void exclusive_scan_i32_counted(int32_t* data, int64_t n_max, const int32_t* nd, hipStream_t stream);
 
 // ------------------------------------------------------------ launches
+// What the build's one synchronisation reads: the cells per level, the sums of
+// the chain lengths and of the group marks, and the error flag.
+constexpr int kStatTotals = 0, kStatFlag = kLevels + 2, kStatWords = kLevels + 3;
 // a1-a2: keys, sort, gather.  Sets bits of the device error flag *d_flag
 // (bit 0: non-finite position, bit 1: bad mass; bit 3: a run of more than
 // kRunMax particles shares the high key word, so the order is incomplete and
@@ -242,14 +288,14 @@ void exclusive_scan_i32_counted(int32_t* data, int64_t n_max, const int32_t* nd,
 void build_sorted(Tree& t, const double* x, const double* y, const double* z, int64_t ps,
                   const double* m, int64_t ms, int32_t* d_flag, bool full, hipStream_t stream);
 // a3-a5; synchronises `stream` once, then makes it wait for t.gathered, and
-// fails with SRF_EDOMAIN if bit 0 or 1 of *d_flag (set by build_sorted) is
-// set.  Returns false, having built nothing, if bit 3 is set.
-bool build_cells_and_groups(Tree& t, int32_t* d_flag, hipStream_t stream);
+// fails with SRF_EDOMAIN if bit 0 or 1 of the flag d_stat[kStatFlag] (set by
+// build_sorted) is set.  Returns false, having built nothing, if bit 3 is set.
+bool build_cells_and_groups(Tree& t, int32_t* d_stat, hipStream_t stream);
 // Tree reuse: positions and masses (m may be NULL: masses kept) gathered in
 // the tree's sorted order into px..pm, wrapped, with the same checks as
-// build_sorted (bits of *d_flag)
+// build_sorted: bad[0] is set for a non-finite position, bad[1] for a bad mass
 void gather_refit(const Tree& t, const double* x, const double* y, const double* z, int64_t ps, const double* m,
-                  int64_t ms, int32_t* d_flag, double* px, double* py, double* pz, double* pm, hipStream_t stream);
+                  int64_t ms, int32_t* bad, double* px, double* py, double* pz, double* pm, hipStream_t stream);
 // moments and cell and group boxes of the tree's current particles, the
 // structure held (asynchronous)
 void refit_cells_and_groups(Tree& t, hipStream_t stream);

@@ -32,7 +32,6 @@
 // margin of a threshold (classify32 below): the decisions, and so the
 // lists, are those of the FP64 expressions.
 #include <type_traits>
-#include <vector>
 
 #include "common.h"
 
@@ -329,7 +328,7 @@ struct ItemWriter {
 constexpr int64_t kSlot = 2048;
 // The totals (particle entries, cell entries, interactions, groups that did
 // not fit) are kept in kTotals rows of four, block b adding to row b mod
-// kTotals, and summed on the host: one row for all groups made the waves'
+// kTotals, and summed at the end: one row for all groups made the waves'
 // walk wait for its atomics (34 ns a group, 1.9 ms at 51000 groups).
 constexpr int kTotals = 256;
 constexpr int kListThreads = 64;   // one wave per block (128 and 256 measured slower)
@@ -490,31 +489,40 @@ __global__ __launch_bounds__(kListThreads) void k_lists(int64_t ng, const double
     }
 }
 
-// The same lists from one wave per group, for trees of at most
-// kWaveWalkGroups groups (the tree then has the slot-ordered records).  The wave keeps the cells its group still has to
+// The same lists from one wave per group (where the tree has the slot-ordered
+// records).  The wave keeps the cells its group still has to
 // look at on a stack in LDS, as level slots; it takes up to 64 of them at a
 // time, one per lane, and pushes the children of those it opens (they are
 // one run of the next level's slots, so their records are read side by
-// side).  Items are collected as they are found, at the other end of the
-// same LDS buffer, and put in preorder at the end by a bitonic sort in
-// registers: the order in which the thread's walk finds them.
+// side).  Items go to the group's slot as they are found, and are put in
+// preorder at the end by a bitonic sort in registers: the order in which the
+// thread's walk finds them.
 //
 // A thread's walk is a chain of dependent loads, one per visited cell: about
 // 1.1 ms for a clustered set of any size below 10^6 particles, with a wave
 // for 64 groups and most of the chip idle.  Here the chain is one load per 64
 // cells, and the waves are 64 times as many.
 // It issues more instructions per group (idle lanes in the top levels, the
-// sort), so that a tree that fills the chip with threads' walks keeps those.
-// k_lists against k_walk, us: 160 / 12 at 4096 uniform particles (96 groups),
-// 1117 / 49 at 131071 clustered ones (3050), 1564 / 436 at 2^21 (51000), 744
-// / 216 at 2^21 on the Zel'dovich lattice (33000), but 1563 / 1578 at 1.3e7
-// clustered (316000) and 1240 / 1660 at 2^24 on the lattice (265000); refitted
-// trees at 2^21: 933 / 331.  The line lies where the two would meet.
-// A group that does not fit the buffer is counted in totals[3] and leaves its
-// list empty; the thread's walk then does the whole tree.
-constexpr int kWaveBuf = 2304;   // items and stack together; 17 waves per CU
-constexpr int kWaveItems = 2048;
-static_assert(kWaveItems <= kSlot, "a wave's items fit a group's slot");
+// sort), so that a tree that fills the chip with threads' walks keeps those,
+// except a deep one, where the threads of a wave wait for the longest walk.
+// k_lists against k_walk, us: 160 / 11 at 4096 uniform particles (96 groups),
+// 1117 / 49 at 131071 clustered ones (3050), 1564 / 383 at 2^21 (51000), 744
+// / 184 at 2^21 on the Zel'dovich lattice (33000), 1594 / 1317 at 1.3e7
+// clustered (316000, 14 levels), but 1214 / 1403 at 2^24 on the lattice
+// (265000, 9 levels); refitted trees at 2^21: 933 / 290.
+// In trees of at most kWideGroups groups a slot holds kWideSlot items (a group
+// of a void beside clumps of a 2 x 10^5 particle set has 2100), and a group of
+// more than kWaveItems leaves them unsorted for k_sort_wide, whose registers
+// would cost this kernel its occupancy; they are counted in the low half of
+// totals[3].  A group that fits neither its slot nor the stack is counted in
+// the high half and leaves its list empty; the thread's walk then does the
+// whole tree.
+constexpr int kWaveStack = 1536;   // 6 KB of LDS
+constexpr int kWaveItems = 2048;   // what the sort takes
+constexpr int64_t kWideSlot = 4096;
+constexpr int64_t kWideGroups = 1 << 16;   // 1 GB of slots
+constexpr unsigned long long kUnsorted = 1ull, kOverflow = 1ull << 32;
+static_assert(kWaveItems == kSlot, "a narrow slot's items are sorted where they are found");
 
 // The value of lane ^ M.
 template <int M>
@@ -557,12 +565,13 @@ __device__ __forceinline__ void bitonic_merge(int (&v)[R], int lane) {
     if constexpr (K < 64 * R) bitonic_merge<R, 2 * K>(v, lane);
 }
 
-// n <= 64 R item keys (2 preorder + accepted) sorted, and written as items.
+// n <= 64 R item keys (2 preorder + accepted) at out sorted, and left there as
+// items.
 template <int R>
-__device__ __forceinline__ void write_sorted(const int32_t* key, int n, int lane, int32_t* __restrict__ out) {
+__device__ __forceinline__ void sort_items(int n, int lane, int32_t* out) {
     int v[R];
 #pragma unroll
-    for (int r = 0; r < R; ++r) v[r] = r * 64 + lane < n ? key[r * 64 + lane] : INT32_MAX;
+    for (int r = 0; r < R; ++r) v[r] = r * 64 + lane < n ? out[r * 64 + lane] : INT32_MAX;
     bitonic_merge<R, 2>(v, lane);
 #pragma unroll
     for (int r = 0; r < R; ++r) {
@@ -579,8 +588,8 @@ __global__ __launch_bounds__(64) void k_walk(int64_t ng, const double* __restric
                                              const double* __restrict__ nZ, const RefitCell* __restrict__ rpack,
                                              double rc2, double th2, int64_t* __restrict__ cnt,
                                              int64_t* __restrict__ icnt, unsigned long long* __restrict__ totals,
-                                             int32_t* __restrict__ items) {
-    __shared__ int32_t buf[kWaveBuf];   // items from the front, the stack from the back
+                                             int32_t* __restrict__ items, int64_t slot) {
+    __shared__ int32_t stack[kWaveStack];   // filled from the back
     const int lane = threadIdx.x;
     const int64_t g = xcd_block(blockIdx.x, gridDim.x);
     const Frame f = group_frame(glo, ghi, g);
@@ -593,54 +602,56 @@ __global__ __launch_bounds__(64) void k_walk(int64_t ng, const double* __restric
     const Bounds32 b32 = bounds32(rc2, th2);
     const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
     totals += 4 * (blockIdx.x & (kTotals - 1));
-    int ni = 0, top = kWaveBuf - 1;   // the stack is buf[top, kWaveBuf)
+    int32_t* out = items + g * slot;
+    int ni = 0, top = kWaveStack - 1;   // the stack is stack[top, kWaveStack)
     uint32_t np = 0, nc = 0;
-    if (lane == 0) buf[top] = 0;   // the root is slot 0
+    if (lane == 0) stack[top] = 0;   // the root is slot 0
     __syncthreads();
-    while (top < kWaveBuf) {
-        const bool on = top + lane < kWaveBuf;
+    while (top < kWaveStack) {
+        const bool on = top + lane < kWaveStack;
         int cls = 0, kids = 0;
         int32_t pre = 0;
         uint32_t a = 0;
         if (on) {
-            const int32_t slot = buf[top + lane];
-            const uint4 r = srec[slot];
-            pre = spre[slot];
+            const int32_t c = stack[top + lane];
+            const uint4 r = srec[c];
+            pre = spre[c];
             const int level = (int)(r.w & 31u);
             kids = (int)(r.w >> 5);
             a = (r.x >> 21) | ((r.y >> 21) << 11) | ((r.z >> 21) << 22);
             cls = classify_slot<COM, REFIT>(r, level, kids == 0, pre, nX, nY, nZ, rpack, f, f32, b32, rc2, th2);
         }
-        top = top + 64 < kWaveBuf ? top + 64 : kWaveBuf;
+        top = top + 64 < kWaveStack ? top + 64 : kWaveStack;
         const bool item = cls == 1 || cls == 2;
         const uint64_t mi = __ballot(item);
         if (cls != 3) kids = 0;
         const int incl = wave_scan(kids);
         const int push = __builtin_amdgcn_readlane(incl, 63), found = __popcll(mi);
-        if (ni + found > kWaveItems || ni + found + push > top) {
+        if (ni + found > slot || push > top) {
             if (lane == 0) {
                 cnt[g] = icnt[g] = 0;
-                atomicAdd(&totals[3], 1ull);
+                atomicAdd(&totals[3], kOverflow);
             }
             return;
         }
         __syncthreads();   // the stack's entries are read before they are overwritten
-        if (item) buf[ni + __popcll(mi & lt)] = 2 * pre + (cls == 1 ? 1 : 0);
+        if (item) out[ni + __popcll(mi & lt)] = 2 * pre + (cls == 1 ? 1 : 0);
         if (cls == 1) ++nc;
         if (cls == 2) np += a;
         ni += found;
         top -= push;
-        int32_t* d = buf + top + incl - kids;
+        int32_t* d = stack + top + incl - kids;
 #pragma unroll
         for (int k = 0; k < 8; ++k)
             if (k < kids) d[k] = (int32_t)a + k;
         __syncthreads();
     }
-    int32_t* out = items + g * kSlot;
-    if (ni <= 256) write_sorted<4>(buf, ni, lane, out);
-    else if (ni <= 512) write_sorted<8>(buf, ni, lane, out);
-    else if (ni <= 1024) write_sorted<16>(buf, ni, lane, out);
-    else write_sorted<32>(buf, ni, lane, out);
+    __threadfence_block();   // the keys are read back by other lanes
+    if (ni <= 256) sort_items<4>(ni, lane, out);
+    else if (ni <= 512) sort_items<8>(ni, lane, out);
+    else if (ni <= 1024) sort_items<16>(ni, lane, out);
+    else if (ni <= kWaveItems) sort_items<32>(ni, lane, out);
+    else if (lane == 0) atomicAdd(&totals[3], kUnsorted);
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) {
         np += __shfl_xor(np, o, 64);
@@ -653,6 +664,71 @@ __global__ __launch_bounds__(64) void k_walk(int64_t ng, const double* __restric
         atomicAdd(&totals[1], (unsigned long long)nc);
         atomicAdd(&totals[2], (unsigned long long)gcount[g] * ((unsigned long long)np + nc));
     }
+}
+
+__global__ __launch_bounds__(64) void k_sort_wide(const int64_t* __restrict__ icnt, int32_t* __restrict__ items) {
+    const int64_t n = icnt[blockIdx.x];
+    if (n > kWaveItems) sort_items<64>((int)n, threadIdx.x, items + blockIdx.x * kWideSlot);
+}
+
+// One block: the totals' rows summed into *host (pinned memory), and, with ng
+// > 0, the exclusive scan of the ng list lengths in place with the total at
+// the end, four lengths a thread at a time.
+constexpr int kScanBlock = 1024;
+constexpr int64_t kScanGroups = 16384;   // one block's scan is shorter than the general one's three launches
+
+__global__ __launch_bounds__(kScanBlock) void k_list_totals(int64_t ng, int64_t* __restrict__ off,
+                                                            const unsigned long long* __restrict__ totals,
+                                                            unsigned long long* __restrict__ host) {
+    __shared__ unsigned long long part[4][kTotals / 64];
+    __shared__ int64_t wsum[kScanBlock / 64];
+    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+    if (tid < kTotals) {
+        unsigned long long v[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            v[k] = totals[4 * tid + k];
+            for (int o = 32; o >= 1; o >>= 1) v[k] += __shfl_xor(v[k], o, 64);
+            if (lane == 0) part[k][wid] = v[k];
+        }
+    }
+    __syncthreads();
+    if (tid < 4) {
+        unsigned long long v = 0;
+        for (int w = 0; w < kTotals / 64; ++w) v += part[tid][w];
+        host[tid] = v;
+    }
+    int64_t carry = 0;
+    for (int64_t c0 = 0; c0 < ng; c0 += 4 * kScanBlock) {
+        const int64_t j = c0 + 4 * (int64_t)tid;
+        int64_t v[4], sum = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            v[k] = j + k < ng ? off[j + k] : 0;
+            sum += v[k];
+        }
+        int64_t incl = sum;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int64_t u = __shfl_up(incl, o, 64);
+            if (lane >= o) incl += u;
+        }
+        if (lane == 63) wsum[wid] = incl;
+        __syncthreads();
+        int64_t at = carry + incl - sum;
+#pragma unroll
+        for (int w = 0; w < kScanBlock / 64; ++w) {
+            at += w < wid ? wsum[w] : 0;
+            carry += wsum[w];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            if (j + k < ng) off[j + k] = at;
+            at += v[k];
+        }
+    }
+    if (tid == 0 && ng > 0) off[ng] = carry;
 }
 
 // Expansion: one wave per group turns its items into entries.  A leaf item
@@ -777,7 +853,9 @@ void build_lists(const Tree& t, Lists& l, hipStream_t st) {
     l.n_groups = ng;
     l.off.alloc(ng + 1, st);
     DevBuf<int64_t> icnt(ng + 1, st);
-    DevBuf<int32_t> slots(ng * kSlot > 0 ? ng * kSlot : 1, st);
+    const bool waves = ng > 0 && t.srec.get();
+    const int64_t slot_items = waves && ng <= kWideGroups ? kWideSlot : kSlot;
+    DevBuf<int32_t> slots(ng > 0 ? ng * slot_items : 1, st);
     DevBuf<unsigned long long> totals(4 * kTotals, st);
     const int B = kListThreads;
     constexpr int G = kGroupsPerThread;
@@ -805,42 +883,47 @@ void build_lists(const Tree& t, Lists& l, hipStream_t st) {
     auto wave_walk = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3((unsigned)ng), dim3(64), 0, st, ng, t.glo.get(), t.ghi.get(), t.gcount.get(),
                            t.srec.get(), t.spre.get(), t.nX.get(), t.nY.get(), t.nZ.get(), t.rpack.get(), rc2, th2,
-                           l.off.get(), icnt.get(), totals.get(), slots.get());
+                           l.off.get(), icnt.get(), totals.get(), slots.get(), slot_items);
     };
     // sizes and items: by waves, and by threads when the tree is past the
     // waves' range or some group's list does not fit a wave's buffer
-    std::vector<unsigned long long> rows(4 * kTotals);
-    unsigned long long h[4];
-    auto count = [&](bool waves) {
+    HostSlot slot(st);
+    const unsigned long long* h = nullptr;
+    auto count = [&](bool by_waves) {
         fill_u64(totals.get(), 0ull, 4 * kTotals, st);
-        if (!waves)
+        if (!by_waves)
             walk_all(std::false_type{}, l.off.get(), icnt.get(), totals.get(), (const int64_t*)nullptr, slots.get());
         else if (t.refit)
             com ? wave_walk(k_walk<true, true>) : wave_walk(k_walk<false, true>);
         else
             com ? wave_walk(k_walk<true, false>) : wave_walk(k_walk<false, false>);
         SRF_HIP(hipGetLastError());
-        exclusive_scan_i64(l.off.get(), ng, true, st);
-        SRF_HIP(hipMemcpyAsync(rows.data(), totals.get(), rows.size() * sizeof(unsigned long long),
-                               hipMemcpyDeviceToHost, st));
-        SRF_HIP(hipStreamSynchronize(st));
-        for (int k = 0; k < 4; ++k) {
-            h[k] = 0;
-            for (int r = 0; r < kTotals; ++r) h[k] += rows[4 * r + k];
-        }
+        const bool one = ng <= kScanGroups;
+        if (!one) exclusive_scan_i64(l.off.get(), ng, true, st);
+        hipLaunchKernelGGL(k_list_totals, dim3(1), dim3(kScanBlock), 0, st, one ? ng : 0, l.off.get(), totals.get(),
+                           slot.device<unsigned long long>());
+        SRF_HIP(hipGetLastError());
+        h = slot.wait<unsigned long long>();
     };
-    const bool waves = ng > 0 && t.srec.get();
     count(waves);
-    if (waves && h[3] != 0) count(false);
+    int64_t slot_now = slot_items;
+    if (waves && h[3] >= kOverflow) {
+        count(false);
+        slot_now = kSlot;
+    }
     l.n_particle_entries = (int64_t)h[0];
     l.n_node_entries = (int64_t)h[1];
     l.n_entries = (int64_t)(h[0] + h[1]);
     l.interactions = (int64_t)h[2];
     l.ent.alloc(l.n_entries > 0 ? l.n_entries : 1, st);
     if (ng == 0) return;
-    if (h[3] == 0) {
+    if (h[3] == 0 || slot_now == kWideSlot) {
         // every group's items fit its slot
-        hipLaunchKernelGGL(k_expand, dim3((unsigned)ng), dim3(64), 0, st, ng, kSlot, icnt.get(),
+        if (h[3] != 0) {
+            hipLaunchKernelGGL(k_sort_wide, dim3((unsigned)ng), dim3(64), 0, st, icnt.get(), slots.get());
+            SRF_HIP(hipGetLastError());
+        }
+        hipLaunchKernelGGL(k_expand, dim3((unsigned)ng), dim3(64), 0, st, ng, slot_now, icnt.get(),
                            (const int64_t*)nullptr, slots.get(), t.range.get(), l.off.get(), l.ent.get());
         SRF_HIP(hipGetLastError());
         return;

@@ -97,13 +97,49 @@ void dev_free(void* p, hipStream_t stream) {
     c.live.erase(it);
 }
 
+namespace {
+std::mutex g_slot_mu;
+std::vector<void*>& free_slots() {
+    static auto* v = new std::vector<void*>();   // never destroyed
+    return *v;
+}
+}  // namespace
+
+static void release_host_slots() {
+    std::lock_guard<std::mutex> lk(g_slot_mu);
+    for (void* p : free_slots()) (void)hipHostFree(p);
+    free_slots().clear();
+}
+
 void dev_release_all() {
+    release_host_slots();
     Cache& c = cache();
     std::lock_guard<std::mutex> lk(c.mu);
     if (c.free_blocks.empty()) return;
     (void)hipDeviceSynchronize();
     for (auto& kv : c.free_blocks) (void)hipFree(kv.second.p);
     c.free_blocks.clear();
+}
+
+void* host_slot_take() {
+    {
+        std::lock_guard<std::mutex> lk(g_slot_mu);
+        auto& v = free_slots();
+        if (!v.empty()) {
+            void* p = v.back();
+            v.pop_back();
+            return p;
+        }
+    }
+    void* p = nullptr;
+    // pinned memory is visible to every device (portable)
+    SRF_HIP(hipHostMalloc(&p, kHostSlotBytes, hipHostMallocPortable));
+    return p;
+}
+
+void host_slot_give(void* p) {
+    std::lock_guard<std::mutex> lk(g_slot_mu);
+    free_slots().push_back(p);
 }
 
 hipStream_t aux_stream() {

@@ -219,15 +219,19 @@ __global__ __launch_bounds__(THREADS) void k_levels(int64_t n, const uint64_t* _
 // In place, over the tiles of k_levels: the exclusive scans of the chain
 // lengths (the preorder number of each chain's first cell) and of the group
 // marks (the group number of each group start), each tile starting from its
-// scanned sum (rows kLevels and kLevels + 1 of blk); entry n of each gets
-// the total.  Thread t takes the tile's entries 4t .. 4t + 3.
+// scanned sum (rows kLevels and kLevels + 1 of blk); each group start also
+// goes to its group's place in gfirst.  Thread t takes the tile's entries 4t ..
+// 4t + 3.
 __global__ __launch_bounds__(kLvThreads) void k_scan_tiles(int64_t n, int64_t nblocks, int32_t* __restrict__ chain,
-                                                           int32_t* __restrict__ mark,
+                                                           const int32_t* __restrict__ mark,
                                                            const int32_t* __restrict__ blk,
-                                                           const int32_t* __restrict__ tot) {
+                                                           int32_t* __restrict__ gfirst,
+                                                           const int32_t* __restrict__ stat,
+                                                           int32_t* __restrict__ host_stat) {
     static_assert(kPer == 4, "four entries per thread");
     __shared__ int32_t wsum[kLvThreads / 64][2];
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+    if (blockIdx.x == 0 && tid < kStatWords) host_stat[tid] = stat[tid];   // read at the build's synchronisation
     const int64_t s0 = blockIdx.x * (int64_t)kLvTile + kPer * tid;
     int32_t c[kPer], m[kPer];
     if (s0 + kPer <= n) {
@@ -266,29 +270,21 @@ __global__ __launch_bounds__(kLvThreads) void k_scan_tiles(int64_t n, int64_t nb
             mo += wsum[w][1];
         }
     }
-    int32_t cx[kPer], mx[kPer];
+    int32_t cx[kPer];
 #pragma unroll
     for (int k = 0; k < kPer; ++k) {
         cx[k] = co;
-        mx[k] = mo;
+        if (m[k]) gfirst[mo] = (int32_t)(s0 + k);
         co += c[k];
         mo += m[k];
     }
     if (s0 + kPer <= n) {
         *reinterpret_cast<int4*>(chain + s0) = make_int4(cx[0], cx[1], cx[2], cx[3]);
-        *reinterpret_cast<int4*>(mark + s0) = make_int4(mx[0], mx[1], mx[2], mx[3]);
     } else {
 #pragma unroll
         for (int k = 0; k < kPer; ++k) {
-            if (s0 + k < n) {
-                chain[s0 + k] = cx[k];
-                mark[s0 + k] = mx[k];
-            }
+            if (s0 + k < n) chain[s0 + k] = cx[k];
         }
-    }
-    if (blockIdx.x == 0 && tid == 0) {
-        chain[n] = tot[kLevels];
-        mark[n] = tot[kLevels + 1];
     }
 }
 
@@ -334,22 +330,6 @@ __global__ __launch_bounds__(256) void k_level_scan(int64_t nblocks, int32_t* __
         carry += total;
     }
     if (tid == 0) tot[blockIdx.x] = carry;
-}
-
-struct Summary {
-    int64_t n_groups;
-    int32_t flag;
-    int32_t pad;
-    int64_t tot[kLevels];    // cells per level
-};
-
-__global__ void k_summary(int64_t n, const int32_t* __restrict__ gscan, const int32_t* __restrict__ flag,
-                          const int32_t* __restrict__ tot, Summary* __restrict__ out) {
-    if (threadIdx.x != 0) return;
-    out->n_groups = gscan[n];
-    out->flag = *flag;
-    out->pad = 0;
-    for (int L = 0; L < kLevels; ++L) out->tot[L] = tot[L];
 }
 
 __device__ __forceinline__ uint32_t compact3(uint64_t v) {
@@ -462,50 +442,51 @@ __device__ __forceinline__ uint4 slot_record(const NodeGeo& g, uint32_t a, int k
 // its two walk records.
 constexpr int kMomLanes = 4;
 
-__global__ __launch_bounds__(256) void k_moments(int32_t lo, int32_t hi, int32_t next_hi, int64_t n, int64_t nn,
-                                                 const int32_t* __restrict__ sfirst, const int32_t* __restrict__ spre,
-                                                 const int32_t* __restrict__ schild,
-                                                 const int32_t* __restrict__ pfirst,
-                                                 const int32_t* __restrict__ start, const double* __restrict__ px,
-                                                 const double* __restrict__ py, const double* __restrict__ pz,
-                                                 const double* __restrict__ pm, int32_t* __restrict__ scount,
-                                                 double* __restrict__ sM, double* __restrict__ sX,
-                                                 double* __restrict__ sY, double* __restrict__ sZ,
-                                                 NodeRange* __restrict__ rng, double* __restrict__ oM,
-                                                 double* __restrict__ oX, double* __restrict__ oY,
-                                                 double* __restrict__ oZ, int32_t* __restrict__ leaf_of,
-                                                 const NodeGeo* __restrict__ geo, uint2* __restrict__ pack,
-                                                 uint4* __restrict__ srec) {
-    const int64_t i = lo + blockIdx.x * (int64_t)(256 / kMomLanes) + threadIdx.x / kMomLanes;
+struct MomentArgs {
+    int64_t n, nn;
+    const int32_t *sfirst, *spre, *schild, *pfirst, *start;
+    const double *px, *py, *pz, *pm;
+    int32_t* scount;
+    double *sM, *sX, *sY, *sZ;
+    NodeRange* rng;
+    double *oM, *oX, *oY, *oZ;
+    int32_t* leaf_of;
+    const NodeGeo* geo;
+    uint2* pack;
+    uint4* srec;
+};
+
+// Cell i of the level [lo, hi); its children lie before next_hi.
+__device__ __forceinline__ void moments_cell(const MomentArgs& a, int64_t i, int32_t lo, int32_t hi, int32_t next_hi) {
     const int j = threadIdx.x & (kMomLanes - 1);
     const bool on = i < hi;
     const int64_t c = on ? i : lo;
-    const int32_t f = sfirst[c], pre = spre[c], ch = schild[c];
+    const int32_t f = a.sfirst[c], pre = a.spre[c], ch = a.schild[c];
     double sm = 0, sx = 0, sy = 0, sz = 0;
     int64_t cnt = 0;
     int kids = 0;
     if (on) {
         if (ch < 0) {
-            const int64_t e = pre + 1 < nn ? pfirst[pre + 1] : n;
+            const int64_t e = pre + 1 < a.nn ? a.pfirst[pre + 1] : a.n;
             for (int64_t s = f + j; s < e; s += kMomLanes) {
-                const double mm = pm[s];
+                const double mm = a.pm[s];
                 sm += mm;
-                sx += mm * px[s];
-                sy += mm * py[s];
-                sz += mm * pz[s];
-                leaf_of[s] = pre;
+                sx += mm * a.px[s];
+                sy += mm * a.py[s];
+                sz += mm * a.pz[s];
+                a.leaf_of[s] = pre;
             }
             cnt = j == 0 ? e - f : 0;
         } else {
-            const int64_t lim = c + 1 < hi ? sfirst[c + 1] : n;   // first particle of the next cell of this level
-            for (int64_t q = ch + j; q < next_hi && sfirst[q] < lim; q += kMomLanes) {
-                sm += sM[q];
-                sx += sX[q];
-                sy += sY[q];
-                sz += sZ[q];
-                cnt += scount[q];
+            const int64_t lim = c + 1 < hi ? a.sfirst[c + 1] : a.n;   // first particle of the next cell of this level
+            for (int64_t q = ch + j; q < next_hi && a.sfirst[q] < lim; q += kMomLanes) {
+                sm += a.sM[q];
+                sx += a.sX[q];
+                sy += a.sY[q];
+                sz += a.sZ[q];
+                cnt += a.scount[q];
                 ++kids;
-                rng[spre[q]].parent = pre;
+                a.rng[a.spre[q]].parent = pre;
             }
         }
     }
@@ -519,24 +500,42 @@ __global__ __launch_bounds__(256) void k_moments(int32_t lo, int32_t hi, int32_t
         kids += __shfl_xor(kids, o, kMomLanes);
     }
     if (on && j == 0) {
-        scount[c] = (int32_t)cnt;
-        sM[c] = sm;
-        sX[c] = sx;
-        sY[c] = sy;
-        sZ[c] = sz;
+        a.scount[c] = (int32_t)cnt;
+        a.sM[c] = sm;
+        a.sX[c] = sx;
+        a.sY[c] = sy;
+        a.sZ[c] = sz;
         const int64_t e = f + cnt;
-        rng[pre].first = f;
-        rng[pre].count = (int32_t)cnt;
-        const int32_t skip = e < n ? start[e] : (int32_t)nn;
-        rng[pre].skip = skip;
-        const NodeGeo g = geo[pre];
-        pack[pre] = walk_record(g, (int32_t)cnt, skip);
-        if (srec) srec[c] = slot_record(g, ch < 0 ? (uint32_t)cnt : (uint32_t)ch, kids);
-        if (pre == 0) rng[pre].parent = -1;
-        oM[pre] = sm;
-        oX[pre] = sx / sm;
-        oY[pre] = sy / sm;
-        oZ[pre] = sz / sm;
+        a.rng[pre].first = f;
+        a.rng[pre].count = (int32_t)cnt;
+        const int32_t skip = e < a.n ? a.start[e] : (int32_t)a.nn;
+        a.rng[pre].skip = skip;
+        const NodeGeo g = a.geo[pre];
+        a.pack[pre] = walk_record(g, (int32_t)cnt, skip);
+        if (a.srec) a.srec[c] = slot_record(g, ch < 0 ? (uint32_t)cnt : (uint32_t)ch, kids);
+        if (pre == 0) a.rng[pre].parent = -1;
+        a.oM[pre] = sm;
+        a.oX[pre] = sx / sm;
+        a.oY[pre] = sy / sm;
+        a.oZ[pre] = sz / sm;
+    }
+}
+
+__global__ __launch_bounds__(256) void k_moments(MomentArgs a, int32_t lo, int32_t hi, int32_t next_hi) {
+    moments_cell(a, lo + blockIdx.x * (int64_t)(256 / kMomLanes) + threadIdx.x / kMomLanes, lo, hi, next_hi);
+}
+
+// Several levels of at most kFewCells cells each, deepest first, by one block:
+// the first levels and, in a clustered set, the last ones, each of which was a
+// launch of its own with a few waves.
+constexpr int kMomBlock = 1024;
+constexpr int32_t kFewCells = 1024;
+__global__ __launch_bounds__(kMomBlock) void k_moments_few(MomentArgs a, LevelBase base, int deepest, int top) {
+    for (int L = deepest; L >= top; --L) {
+        const int32_t lo = base.off[L], hi = base.off[L + 1], next_hi = L < kMaxLevel ? base.off[L + 2] : hi;
+        for (int64_t i = lo; i < hi; i += kMomBlock / kMomLanes)
+            moments_cell(a, i + threadIdx.x / kMomLanes, lo, hi, next_hi);
+        __syncthreads();   // the level's sums are read by the next one's cells
     }
 }
 
@@ -679,28 +678,16 @@ __global__ void k_refit_pack(int64_t nn, const NodeGeo* __restrict__ geo, const 
     out[c] = r;
 }
 
-__global__ void k_group_write(int64_t n, const int32_t* __restrict__ sc, int32_t* __restrict__ gfirst) {
-    int64_t s = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (s >= n) return;
-    if (sc[s + 1] != sc[s]) gfirst[sc[s]] = (int32_t)s;
-}
-
-__global__ void k_group_count(int64_t ng, int64_t n, const int32_t* __restrict__ gfirst, int32_t* __restrict__ gcount) {
-    int64_t g = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (g >= ng) return;
-    int32_t e = (g + 1 < ng) ? gfirst[g + 1] : (int32_t)n;
-    gcount[g] = e - gfirst[g];
-}
-
 // Tight boxes: 16 lanes per group, lane j taking the group's particles
 // j, j + 16, ... (min and max are exact in any order).  In a refitted tree
 // (REFIT) each position is first moved to its periodic image nearest the
-// group's first particle.
+// group's first particle; in a fresh one the groups' firsts and counts are
+// taken from `starts` (each group's first particle, in order).
 constexpr int kBoxLanes = 16;
 
 template <bool REFIT>
-__global__ __launch_bounds__(256) void k_group_bbox(int64_t ng, const int32_t* __restrict__ gfirst,
-                                                    const int32_t* __restrict__ gcount, const double* __restrict__ px,
+__global__ __launch_bounds__(256) void k_group_bbox(int64_t ng, int64_t n, const int32_t* __restrict__ starts,
+                                                    int32_t* __restrict__ gfirst, int32_t* __restrict__ gcount, const double* __restrict__ px,
                                                     const double* __restrict__ py, const double* __restrict__ pz,
                                                     double* __restrict__ lo, double* __restrict__ hi) {
     const int64_t g = blockIdx.x * (int64_t)(256 / kBoxLanes) + threadIdx.x / kBoxLanes;
@@ -712,7 +699,18 @@ __global__ __launch_bounds__(256) void k_group_bbox(int64_t ng, const int32_t* _
         b[k] = -INFINITY;
     }
     if (g < ng) {
-        const int32_t f = gfirst[g], cnt = gcount[g];
+        int32_t f, cnt;
+        if (REFIT) {
+            f = gfirst[g];
+            cnt = gcount[g];
+        } else {
+            f = starts[g];
+            cnt = (g + 1 < ng ? starts[g + 1] : (int32_t)n) - f;
+            if (j == 0) {
+                gfirst[g] = f;
+                gcount[g] = cnt;
+            }
+        }
         const double r[3] = {px[f], py[f], pz[f]};
         for (int32_t q = j; q < cnt; q += kBoxLanes) {
             double v[3] = {px[f + q], py[f + q], pz[f + q]};
@@ -745,14 +743,13 @@ __global__ __launch_bounds__(256) void k_group_bbox(int64_t ng, const int32_t* _
 
 }  // namespace
 
-bool build_cells_and_groups(Tree& t, int32_t* d_flag, hipStream_t st) {
+bool build_cells_and_groups(Tree& t, int32_t* d_stat, hipStream_t st) {
     const int64_t n = t.n;
-    const int B = 256;
     const int64_t nblocks = (n + kLvTile - 1) / kLvTile;
+    HostSlot slot(st);
     // per-particle levels, chain lengths and group starts; per-block cell counts
     DevBuf<int8_t> delta(n, st), leaflv(n, st);
-    DevBuf<int32_t> start(n + 1, st), mark(n + 1, st), blk((kLevels + 2) * nblocks, st), tot(kLevels + 2, st);
-    DevBuf<Summary> dsum(1, st);
+    DevBuf<int32_t> start(n, st), mark(n, st), starts(n, st), blk((kLevels + 2) * nblocks, st);
     auto levels = [&](auto kernel, int threads) {
         hipLaunchKernelGGL(kernel, dim3((unsigned)nblocks), dim3(threads), 0, st, n, t.keys.get(), t.n_leaf, t.n_group,
                            nblocks, delta.get(), leaflv.get(), start.get(), mark.get(), blk.get());
@@ -764,23 +761,19 @@ bool build_cells_and_groups(Tree& t, int32_t* d_flag, hipStream_t st) {
     if (nblocks <= 512) levels(k_levels<1024>, 1024);
     else levels(k_levels<256>, 256);
     SRF_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_level_scan, dim3(kLevels + 2), dim3(256), 0, st, nblocks, blk.get(), tot.get());
+    hipLaunchKernelGGL(k_level_scan, dim3(kLevels + 2), dim3(256), 0, st, nblocks, blk.get(), d_stat + kStatTotals);
     SRF_HIP(hipGetLastError());
-    // preorder number of each chain's first cell, group number of each group start
+    // preorder number of each chain's first cell, first particle of each group
     hipLaunchKernelGGL(k_scan_tiles, dim3((unsigned)nblocks), dim3(kLvThreads), 0, st, n, nblocks, start.get(),
-                       mark.get(), blk.get(), tot.get());
-    SRF_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_summary, dim3(1), dim3(64), 0, st, n, mark.get(), d_flag, tot.get(), dsum.get());
+                       mark.get(), blk.get(), starts.get(), d_stat, slot.device<int32_t>());
     SRF_HIP(hipGetLastError());
     // the one synchronisation: sizes and the device's check of the inputs
-    Summary hs;
-    SRF_HIP(hipMemcpyAsync(&hs, dsum.get(), sizeof(Summary), hipMemcpyDeviceToHost, st));
-    SRF_HIP(hipStreamSynchronize(st));
+    const int32_t* hs = slot.wait<int32_t>();
     // the cells below read the sorted positions, gathered on the second stream
     if (t.gathered) SRF_HIP(hipStreamWaitEvent(st, t.gathered, 0));
-    if (hs.flag & 1) fail(SRF_EDOMAIN, "non-finite particle position");
-    if (hs.flag & 2) fail(SRF_EDOMAIN, "particle mass not finite and > 0");
-    if (hs.flag & 8) return false;   // the order is incomplete (see build_sorted)
+    if (hs[kStatFlag] & 1) fail(SRF_EDOMAIN, "non-finite particle position");
+    if (hs[kStatFlag] & 2) fail(SRF_EDOMAIN, "particle mass not finite and > 0");
+    if (hs[kStatFlag] & 8) return false;   // the order is incomplete (see build_sorted)
     // (a level holds fewer than 2^31 cells: its per-block counts are exact
     // int32 sums of counts below n; the total is checked here)
     LevelBase base;
@@ -788,13 +781,13 @@ bool build_cells_and_groups(Tree& t, int32_t* d_flag, hipStream_t st) {
     int max_level = 0;
     for (int L = 0; L < kLevels; ++L) {
         base.off[L] = (int32_t)(acc < INT32_MAX ? acc : INT32_MAX);
-        acc += hs.tot[L];
-        if (hs.tot[L] > 0) max_level = L;
+        acc += hs[kStatTotals + L];
+        if (hs[kStatTotals + L] > 0) max_level = L;
     }
     if (acc > (int64_t)INT32_MAX - 1)
         fail(SRF_EINVAL, "the tree would hold " + std::to_string(acc) + " cells, past 32-bit cell indices");
     base.off[kLevels] = (int32_t)acc;
-    const int64_t nn = acc, ng = hs.n_groups;
+    const int64_t nn = acc, ng = hs[kStatTotals + kLevels + 1];
     t.n_nodes = nn;
     t.n_groups = ng;
     t.max_level = max_level;
@@ -812,61 +805,70 @@ bool build_cells_and_groups(Tree& t, int32_t* d_flag, hipStream_t st) {
     t.sfirst.alloc(nn, st);
     t.spre.alloc(nn, st);
     t.schild.alloc(nn, st);
-    if (ng <= kWaveWalkGroups && nn < kWaveWalkCells) t.srec.alloc(nn, st);
+    int uniform_level = 0;   // of a uniform set's leaves
+    while ((n >> (3 * uniform_level)) > t.n_leaf) ++uniform_level;
+    const bool deep = max_level >= uniform_level + kDeepLevels && ng <= kDeepWalkGroups;
+    if ((ng <= kWaveWalkGroups || deep) && nn < kWaveWalkCells) t.srec.alloc(nn, st);
     for (int L = 0; L <= kLevels; ++L) t.level_off[L] = base.off[L];
     int32_t* sfirst = t.sfirst.get();
     int32_t* spre = t.spre.get();
     int32_t* schild = t.schild.get();
     DevBuf<int32_t> pfirst(nn, st), scount(nn, st);
     DevBuf<double> sM(nn, st), sX(nn, st), sY(nn, st), sZ(nn, st);
-    // the point after which the second stream may build the groups
-    hipStream_t aux = aux_stream();
-    SRF_HIP(hipEventCreateWithFlags(&t.sized, hipEventDisableTiming));
-    SRF_HIP(hipEventCreateWithFlags(&t.grouped, hipEventDisableTiming));
-    SRF_HIP(hipEventRecord(t.sized, st));
+    // the groups' kernel runs beside the cells on the second stream where the
+    // gather did; a small tree's would end before the events are recorded
+    const bool two = t.gathered != nullptr;
+    hipStream_t aux = two ? aux_stream() : st;
+    if (two) {
+        SRF_HIP(hipEventCreateWithFlags(&t.sized, hipEventDisableTiming));
+        SRF_HIP(hipEventCreateWithFlags(&t.grouped, hipEventDisableTiming));
+        SRF_HIP(hipEventRecord(t.sized, st));
+    }
 
     hipLaunchKernelGGL(k_cells, dim3((unsigned)nblocks), dim3(kLvThreads), 0, st, n, nblocks, t.keys.get(),
                        delta.get(), leaflv.get(), start.get(), base, blk.get(), t.geo.get(), pfirst.get(),
                        t.prefix.get(), sfirst, spre, schild);
     SRF_HIP(hipGetLastError());
+    const MomentArgs ma{n, nn, sfirst, spre, schild, pfirst.get(), start.get(), t.px.get(), t.py.get(), t.pz.get(),
+                        t.pm.get(), scount.get(), sM.get(), sX.get(), sY.get(), sZ.get(), t.range.get(), t.nM.get(),
+                        t.nX.get(), t.nY.get(), t.nZ.get(), t.leaf_of.get(), t.geo.get(), t.pack.get(), t.srec.get()};
+    auto cells_of = [&](int L) { return base.off[L + 1] - base.off[L]; };
     for (int L = max_level; L >= 0; --L) {
-        const int32_t lo = base.off[L], hi = base.off[L + 1];
-        if (hi <= lo) continue;
-        const int32_t next_hi = L < kMaxLevel ? base.off[L + 2] : hi;
-        hipLaunchKernelGGL(k_moments, dim3(grid_for(hi - lo, 256 / kMomLanes, 1 << 30)), dim3(256), 0, st, lo, hi,
-                           next_hi, n, nn, sfirst, spre, schild, pfirst.get(), start.get(),
-                           t.px.get(), t.py.get(), t.pz.get(), t.pm.get(), scount.get(), sM.get(), sX.get(), sY.get(),
-                           sZ.get(), t.range.get(), t.nM.get(), t.nX.get(), t.nY.get(), t.nZ.get(), t.leaf_of.get(),
-                           t.geo.get(), t.pack.get(), t.srec.get());
+        int top = L;   // levels L down to top in one launch
+        while (cells_of(L) <= kFewCells && top > 0 && cells_of(top - 1) <= kFewCells) --top;
+        if (cells_of(L) <= kFewCells) {
+            hipLaunchKernelGGL(k_moments_few, dim3(1), dim3(kMomBlock), 0, st, ma, base, L, top);
+            L = top;
+        } else {
+            const int32_t lo = base.off[L], hi = base.off[L + 1];
+            hipLaunchKernelGGL(k_moments, dim3(grid_for(hi - lo, 256 / kMomLanes, 1 << 30)), dim3(256), 0, st, ma, lo,
+                               hi, L < kMaxLevel ? base.off[L + 2] : hi);
+        }
         SRF_HIP(hipGetLastError());
     }
 
-    // groups (from the marks and the sorted positions alone) on the second
-    // stream, beside the cells (queued after them: the cells are the longer
-    // chain)
+    // groups (from their first particles and the sorted positions alone),
+    // queued after the cells, which are the longer chain
     t.gfirst.alloc(ng, st);
     t.gcount.alloc(ng, st);
     t.glo.alloc(ng * 3, st);
     t.ghi.alloc(ng * 3, st);
     // on every way out (an error included) `grouped` marks all the work
     // queued on the second stream, and the build's stream waits for it
-    // before the marks are freed (declared after them, so destroyed first)
+    // before the starts are freed (declared after them, so destroyed first)
     struct JoinAtExit {
         hipStream_t st, aux;
         hipEvent_t e;
         ~JoinAtExit() {
+            if (!e) return;
             (void)hipEventRecord(e, aux);
             (void)hipStreamWaitEvent(st, e, 0);
         }
     } join{st, aux, t.grouped};
-    SRF_HIP(hipStreamWaitEvent(aux, t.sized, 0));
-    hipLaunchKernelGGL(k_group_write, dim3(grid_for(n, B, 1 << 30)), dim3(B), 0, aux, n, mark.get(), t.gfirst.get());
-    SRF_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_group_count, dim3(grid_for(ng, B, 1 << 30)), dim3(B), 0, aux, ng, n, t.gfirst.get(),
-                       t.gcount.get());
-    SRF_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_group_bbox<false>, dim3(grid_for(ng, 256 / kBoxLanes, 1 << 30)), dim3(256), 0, aux, ng,
-                       t.gfirst.get(), t.gcount.get(), t.px.get(), t.py.get(), t.pz.get(), t.glo.get(), t.ghi.get());
+    if (two) SRF_HIP(hipStreamWaitEvent(aux, t.sized, 0));
+    hipLaunchKernelGGL(k_group_bbox<false>, dim3(grid_for(ng, 256 / kBoxLanes, 1 << 30)), dim3(256), 0, aux, ng, n,
+                       starts.get(), t.gfirst.get(), t.gcount.get(), t.px.get(), t.py.get(), t.pz.get(), t.glo.get(),
+                       t.ghi.get());
     SRF_HIP(hipGetLastError());
     return true;
 }
@@ -893,9 +895,9 @@ void refit_cells_and_groups(Tree& t, hipStream_t st) {
                        t.range.get(), t.clo.get(), t.chi.get(), t.rpack.get());
     SRF_HIP(hipGetLastError());
     if (ng > 0) {
-        hipLaunchKernelGGL(k_group_bbox<true>, dim3(grid_for(ng, 256 / kBoxLanes, 1 << 30)), dim3(256), 0, st, ng,
-                           t.gfirst.get(), t.gcount.get(), t.px.get(), t.py.get(), t.pz.get(), t.glo.get(),
-                           t.ghi.get());
+        hipLaunchKernelGGL(k_group_bbox<true>, dim3(grid_for(ng, 256 / kBoxLanes, 1 << 30)), dim3(256), 0, st, ng, n,
+                           (const int32_t*)nullptr, t.gfirst.get(), t.gcount.get(), t.px.get(), t.py.get(),
+                           t.pz.get(), t.glo.get(), t.ghi.get());
         SRF_HIP(hipGetLastError());
     }
 }

@@ -12,33 +12,34 @@ import oracle
 import paper_1211_4406_amd as srf
 import synth
 
-SIZES = [(0.03, 0, 256), (0.07, 257, 512), (0.13, 513, 1024), (0.23, 1025, 2048), (0.245, 2049, 6000)]
+SIZES = [(0.03, 0, 256, 6001), (0.07, 257, 512, 6001), (0.13, 513, 1024, 6001), (0.23, 1025, 2048, 6001),
+         (0.245, 2049, 4096, 6001), (0.245, 4097, 20000, 40001)]
 
 
-def _set(r_cut, n_leaf=1):
+def _set(r_cut, n):
     rng = np.random.default_rng(77)
-    pos = rng.random((6001, 3))
-    p = synth.Params(1.0, r_cut, 1e-3, 0.25, 64, n_leaf)
-    return synth.ParticleSet(pos[:, 0].copy(), pos[:, 1].copy(), pos[:, 2].copy(), np.full(6001, 1.0 / 6001), p)
+    pos = rng.random((n, 3))
+    p = synth.Params(1.0, r_cut, 1e-3, 0.25, 64, 1)
+    return synth.ParticleSet(pos[:, 0].copy(), pos[:, 1].copy(), pos[:, 2].copy(), np.full(n, 1.0 / n), p)
 
 
 def _items(lists):
     return np.diff(lists.poff) + np.diff(lists.noff)
 
 
-@pytest.mark.parametrize("r_cut,lo,hi", SIZES)
-def test_item_counts_reach_each_size(r_cut, lo, hi):
-    ps = _set(r_cut)
+@pytest.mark.parametrize("r_cut,lo,hi,n", SIZES)
+def test_item_counts_reach_each_size(r_cut, lo, hi, n):
+    ps = _set(r_cut, n)
     ot = oracle.OracleTree(ps.x, ps.y, ps.z, ps.m, ps.params)
     assert lo <= _items(ot.lists).max() <= hi, _items(ot.lists).max()
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("r_cut,lo,hi", SIZES)
+@pytest.mark.parametrize("r_cut,lo,hi,n", SIZES)
 @pytest.mark.parametrize("refit", [False, True])
-def test_lists_of_every_size(r_cut, lo, hi, refit):
-    ps = _set(r_cut)
-    print(f"[gpu] walk r_cut={r_cut} refit={refit}", flush=True)
+def test_lists_of_every_size(r_cut, lo, hi, n, refit):
+    ps = _set(r_cut, n)
+    print(f"[gpu] walk r_cut={r_cut} n={n} refit={refit}", flush=True)
     p = srf.Params.of(ps.params)
     x = torch.tensor(ps.positions(), device="cuda")
     tree = srf.tree_build(x, torch.tensor(ps.m, device="cuda"), p)
