@@ -75,7 +75,8 @@ constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / 64;
 constexpr int kItems = 16;   // keys per thread: tiles of 4096 (8 and 12 measured no faster at 2^24)
 constexpr int kFewItems = 4; // and for at most kFewKeys keys, where a tile's latency counts: tiles of 1024
-constexpr int64_t kFewKeys = 1 << 19;
+constexpr int64_t kFewKeys = 1 << 21;
+constexpr int64_t kSelfTiles = 64;   // past which the sums cost more than the scan's launch
 constexpr int kDigits = 256;
 static_assert(kThreads == kDigits, "one digit per thread in the per-digit steps");
 
@@ -446,7 +447,8 @@ __global__ void k_sorted_keys(int64_t n, const int32_t* __restrict__ perm, const
 // few us of latency, for what is a few us of work here; for many particles the
 // compacted runs are read faster.)  Whole forward pass, us, with the general
 // kernels / these and the small tiles: 4096 particles 365 / 295, 20001 500 /
-// 410, 131071 697 / 620, 262139 910 / 840, 524287 1252 / 1241, 10^6 2000 / 2098.
+// 410, 131071 697 / 620, 262139 910 / 840; the passes' sums past kSelfTiles by
+// the scan, 524287 1170 / 1095, 10^6 1919 / 1899, 2^21 3501 / 3464.
 __global__ void k_finish(int64_t n, const uint32_t* __restrict__ hi, const int32_t* __restrict__ idx,
                          const uint32_t* __restrict__ klo, const double* __restrict__ x, const double* __restrict__ y,
                          const double* __restrict__ z, int64_t ps, const double* __restrict__ m, int64_t ms,
@@ -556,7 +558,8 @@ void build_sorted(Tree& t, const double* x, const double* y, const double* z, in
                                tiles, counts.get(), dtot.get());
             SRF_HIP(hipGetLastError());
         };
-        if (few) run(k_hist<kFewItems, true>, k_scatter<false, kFewItems, true>, false);
+        if (few && tiles <= kSelfTiles) run(k_hist<kFewItems, true>, k_scatter<false, kFewItems, true>, false);
+        else if (few) run(k_hist<kFewItems, false>, k_scatter<false, kFewItems, false>, true);
         else if (h) run(k_hist<kItems, false>, k_scatter<true, kItems, false>, true);
         else run(k_hist<kItems, false>, k_scatter<false, kItems, false>, true);
     };

@@ -456,38 +456,55 @@ struct MomentArgs {
     uint4* srec;
 };
 
-// Cell i of the level [lo, hi); its children lie before next_hi.
+// Cell i of the slots [lo, hi): a leaf (LEAF), or an inner cell of the level
+// [lo, hi), whose children lie before next_hi; the others are passed by.
+template <bool LEAF>
 __device__ __forceinline__ void moments_cell(const MomentArgs& a, int64_t i, int32_t lo, int32_t hi, int32_t next_hi) {
     const int j = threadIdx.x & (kMomLanes - 1);
-    const bool on = i < hi;
-    const int64_t c = on ? i : lo;
+    const int64_t c = i < hi ? i : lo;
     const int32_t f = a.sfirst[c], pre = a.spre[c], ch = a.schild[c];
+    const bool on = i < hi && (ch < 0) == LEAF;
     double sm = 0, sx = 0, sy = 0, sz = 0;
     int64_t cnt = 0;
     int kids = 0;
-    if (on) {
-        if (ch < 0) {
-            const int64_t e = pre + 1 < a.nn ? a.pfirst[pre + 1] : a.n;
-            for (int64_t s = f + j; s < e; s += kMomLanes) {
-                const double mm = a.pm[s];
-                sm += mm;
-                sx += mm * a.px[s];
-                sy += mm * a.py[s];
-                sz += mm * a.pz[s];
-                a.leaf_of[s] = pre;
-            }
-            cnt = j == 0 ? e - f : 0;
-        } else {
-            const int64_t lim = c + 1 < hi ? a.sfirst[c + 1] : a.n;   // first particle of the next cell of this level
-            for (int64_t q = ch + j; q < next_hi && a.sfirst[q] < lim; q += kMomLanes) {
-                sm += a.sM[q];
-                sx += a.sX[q];
-                sy += a.sY[q];
-                sz += a.sZ[q];
-                cnt += a.scount[q];
-                ++kids;
-                a.rng[a.spre[q]].parent = pre;
-            }
+    if (LEAF && on) {
+        const int64_t e = pre + 1 < a.nn ? a.pfirst[pre + 1] : a.n;
+        for (int64_t s = f + j; s < e; s += kMomLanes) {
+            const double mm = a.pm[s];
+            sm += mm;
+            sx += mm * a.px[s];
+            sy += mm * a.py[s];
+            sz += mm * a.pz[s];
+            a.leaf_of[s] = pre;
+        }
+        cnt = j == 0 ? e - f : 0;
+    }
+    if (!LEAF && on) {
+        const int64_t lim = c + 1 < hi ? a.sfirst[c + 1] : a.n;   // first particle of the next cell of this level
+        // a cell has at most eight children: two for each lane, loaded together
+        int32_t qf[2], qn[2], qp[2];
+        double v[2][4];
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const int32_t q = ch + j + k * kMomLanes < next_hi ? ch + j + k * kMomLanes : next_hi - 1;
+            qf[k] = ch + j + k * kMomLanes < next_hi ? a.sfirst[q] : INT32_MAX;
+            qn[k] = a.scount[q];
+            qp[k] = a.spre[q];
+            v[k][0] = a.sM[q];
+            v[k][1] = a.sX[q];
+            v[k][2] = a.sY[q];
+            v[k][3] = a.sZ[q];
+        }
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            if (qf[k] >= lim) continue;
+            sm += v[k][0];
+            sx += v[k][1];
+            sy += v[k][2];
+            sz += v[k][3];
+            cnt += qn[k];
+            ++kids;
+            a.rng[qp[k]].parent = pre;
         }
     }
 #pragma unroll
@@ -512,7 +529,7 @@ __device__ __forceinline__ void moments_cell(const MomentArgs& a, int64_t i, int
         a.rng[pre].skip = skip;
         const NodeGeo g = a.geo[pre];
         a.pack[pre] = walk_record(g, (int32_t)cnt, skip);
-        if (a.srec) a.srec[c] = slot_record(g, ch < 0 ? (uint32_t)cnt : (uint32_t)ch, kids);
+        if (a.srec) a.srec[c] = slot_record(g, LEAF ? (uint32_t)cnt : (uint32_t)ch, kids);
         if (pre == 0) a.rng[pre].parent = -1;
         a.oM[pre] = sm;
         a.oX[pre] = sx / sm;
@@ -521,20 +538,24 @@ __device__ __forceinline__ void moments_cell(const MomentArgs& a, int64_t i, int
     }
 }
 
+template <bool LEAF>
 __global__ __launch_bounds__(256) void k_moments(MomentArgs a, int32_t lo, int32_t hi, int32_t next_hi) {
-    moments_cell(a, lo + blockIdx.x * (int64_t)(256 / kMomLanes) + threadIdx.x / kMomLanes, lo, hi, next_hi);
+    moments_cell<LEAF>(a, lo + blockIdx.x * (int64_t)(256 / kMomLanes) + threadIdx.x / kMomLanes, lo, hi, next_hi);
 }
 
 // Several levels of at most kFewCells cells each, deepest first, by one block:
 // the first levels and, in a clustered set, the last ones, each of which was a
-// launch of its own with a few waves.
+// launch of its own with a few waves.  The leaves, most of the cells and of the
+// time, come before in one launch, so that a level waits only for its
+// children's sums (10007 clustered particles: 52 us with the leaves among the
+// levels, 33 us).
 constexpr int kMomBlock = 1024;
 constexpr int32_t kFewCells = 1024;
 __global__ __launch_bounds__(kMomBlock) void k_moments_few(MomentArgs a, LevelBase base, int deepest, int top) {
     for (int L = deepest; L >= top; --L) {
         const int32_t lo = base.off[L], hi = base.off[L + 1], next_hi = L < kMaxLevel ? base.off[L + 2] : hi;
         for (int64_t i = lo; i < hi; i += kMomBlock / kMomLanes)
-            moments_cell(a, i + threadIdx.x / kMomLanes, lo, hi, next_hi);
+            moments_cell<false>(a, i + threadIdx.x / kMomLanes, lo, hi, next_hi);
         __syncthreads();   // the level's sums are read by the next one's cells
     }
 }
@@ -832,8 +853,12 @@ bool build_cells_and_groups(Tree& t, int32_t* d_stat, hipStream_t st) {
     const MomentArgs ma{n, nn, sfirst, spre, schild, pfirst.get(), start.get(), t.px.get(), t.py.get(), t.pz.get(),
                         t.pm.get(), scount.get(), sM.get(), sX.get(), sY.get(), sZ.get(), t.range.get(), t.nM.get(),
                         t.nX.get(), t.nY.get(), t.nZ.get(), t.leaf_of.get(), t.geo.get(), t.pack.get(), t.srec.get()};
+    // the leaves of every level at once, then the inner cells bottom-up
+    hipLaunchKernelGGL(k_moments<true>, dim3(grid_for(nn, 256 / kMomLanes, 1 << 30)), dim3(256), 0, st, ma, 0,
+                       (int32_t)nn, (int32_t)nn);
+    SRF_HIP(hipGetLastError());
     auto cells_of = [&](int L) { return base.off[L + 1] - base.off[L]; };
-    for (int L = max_level; L >= 0; --L) {
+    for (int L = max_level - 1; L >= 0; --L) {   // (the deepest level has leaves only)
         int top = L;   // levels L down to top in one launch
         while (cells_of(L) <= kFewCells && top > 0 && cells_of(top - 1) <= kFewCells) --top;
         if (cells_of(L) <= kFewCells) {
@@ -841,7 +866,7 @@ bool build_cells_and_groups(Tree& t, int32_t* d_stat, hipStream_t st) {
             L = top;
         } else {
             const int32_t lo = base.off[L], hi = base.off[L + 1];
-            hipLaunchKernelGGL(k_moments, dim3(grid_for(hi - lo, 256 / kMomLanes, 1 << 30)), dim3(256), 0, st, ma, lo,
+            hipLaunchKernelGGL(k_moments<false>, dim3(grid_for(hi - lo, 256 / kMomLanes, 1 << 30)), dim3(256), 0, st, ma, lo,
                                hi, L < kMaxLevel ? base.off[L + 2] : hi);
         }
         SRF_HIP(hipGetLastError());

@@ -11,7 +11,7 @@ import oracle
 import paper_1211_4406_amd as srf
 
 pytestmark = pytest.mark.gpu
-FEW = 1 << 19
+FEW = 1 << 21
 
 
 @pytest.mark.parametrize("n,clump", [(1, 0), (2, 2), (63, 0), (64, 64), (1023, 300), (1024, 1024), (1025, 1025),
