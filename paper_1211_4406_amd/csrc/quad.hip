@@ -23,6 +23,7 @@
 // 256 entries, split near/far as in the force kernel), which adds G times
 // the term to the accelerations.
 #include "common.h"
+#include "group.h"
 
 namespace srf {
 namespace {
@@ -239,24 +240,34 @@ __device__ __forceinline__ void quad_pair(const V4& p, const V4& s1, const V2& s
 
 constexpr int kQChunk = 256;   // list entries scanned per compaction round
 
+// LDS of one wave: a chunk's cells.
 template <class T>
-__global__ __launch_bounds__(64) void k_quadrupole(const int32_t* __restrict__ gfirst,
-                                                   const int32_t* __restrict__ gcount,
-                                                   const double* __restrict__ glo, const double* __restrict__ ghi,
-                                                   const int64_t* __restrict__ off, const int32_t* __restrict__ ent,
-                                                   const int32_t* __restrict__ perm, const double* __restrict__ px,
-                                                   const double* __restrict__ py, const double* __restrict__ pz,
-                                                   const double* __restrict__ nX, const double* __restrict__ nY,
-                                                   const double* __restrict__ nZ, const double* __restrict__ S,
-                                                   QCoef<T> c, double far2, double G, double* __restrict__ ax,
-                                                   double* __restrict__ ay, double* __restrict__ az, int64_t os) {
+struct QuadShared {
+    typename QV4<T>::type cp[kQChunk], cs1[kQChunk];
+    typename QV2<T>::type cs2[kQChunk];
+};
+
+// A block of W waves takes one group, its chunks dealt to the waves, whose
+// FP64 sums are added in order.  Cells that reach no target of the group,
+// whose terms are exactly zero, are left out of a chunk.
+// Force with quadrupoles, whole pass, with one wave and all cells / so: 518 /
+// 420 us at 20001 clustered particles, 789 / 735 at 131071, 1683 / 1620 at
+// 524287, 5.37 / 5.25 ms at 2^21.
+template <class T, int W>
+__global__ __launch_bounds__(64 * W) void k_quadrupole(
+    const int32_t* __restrict__ gfirst, const int32_t* __restrict__ gcount, const double* __restrict__ glo,
+    const double* __restrict__ ghi, const int64_t* __restrict__ off, const int32_t* __restrict__ ent,
+    const int32_t* __restrict__ perm, const double* __restrict__ px, const double* __restrict__ py,
+    const double* __restrict__ pz, const double* __restrict__ nX, const double* __restrict__ nY,
+    const double* __restrict__ nZ, const double* __restrict__ S, QCoef<T> c, double far2, double G,
+    double* __restrict__ ax, double* __restrict__ ay, double* __restrict__ az, int64_t os) {
     using V4 = typename QV4<T>::type;
     using V2 = typename QV2<T>::type;
-    __shared__ V4 cp[kQChunk];
-    __shared__ V4 cs1[kQChunk];
-    __shared__ V2 cs2[kQChunk];
-    const int64_t g = blockIdx.x;
-    const int lane = threadIdx.x;
+    __shared__ QuadShared<T> sh_all[W];
+    const int64_t g = xcd_block(blockIdx.x, gridDim.x);
+    const int lane = threadIdx.x & 63;
+    const int wave = W == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    QuadShared<T>& sh = sh_all[wave];
     const int32_t first = gfirst[g], cnt = gcount[g];
     const double cx = (glo[g * 3 + 0] + ghi[g * 3 + 0]) * 0.5;
     const double cy = (glo[g * 3 + 1] + ghi[g * 3 + 1]) * 0.5;
@@ -264,22 +275,23 @@ __global__ __launch_bounds__(64) void k_quadrupole(const int32_t* __restrict__ g
     const double hx = (ghi[g * 3 + 0] - glo[g * 3 + 0]) * 0.5;
     const double hy = (ghi[g * 3 + 1] - glo[g * 3 + 1]) * 0.5;
     const double hz = (ghi[g * 3 + 2] - glo[g * 3 + 2]) * 0.5;
+    const double drop2 = drop_d2(far2, hx, hy, hz);
     const int32_t me = first + (lane < cnt ? lane : 0);
     const T xi = (T)image(px[me] - cx), yi = (T)image(py[me] - cy), zi = (T)image(pz[me] - cz);
     const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
     const QCoef<T> cq = q_pinned(c);
     double sx = 0, sy = 0, sz = 0;
     const int64_t e0 = off[g], e1 = off[g + 1];
-    for (int64_t tb = e0; tb < e1; tb += kQChunk) {
+    for (int64_t tb = e0 + (int64_t)wave * kQChunk; tb < e1; tb += W * kQChunk) {
         const int len = (int)((e1 - tb) < kQChunk ? (e1 - tb) : kQChunk);
-        __syncthreads();
+        lds_order();
         // cells compacted: near ones from the front, far ones (distance from
         // the centre of mass to the group box >= r_cut / 2) from the back
         int nnear = 0, nfar = 0;
         for (int k0 = 0; k0 < len; k0 += 64) {
             const int k = k0 + lane;
             const int32_t v = k < len ? ent[tb + k] : 0;
-            const bool cell = v < 0;
+            bool cell = v < 0;
             double rx = 0, ry = 0, rz = 0;
             bool far = false;
             int64_t q = 0;
@@ -293,7 +305,9 @@ __global__ __launch_bounds__(64) void k_quadrupole(const int32_t* __restrict__ g
                 rz -= rint(rz);
                 const double ex = fmax(fabs(rx) - hx, 0.0), ey = fmax(fabs(ry) - hy, 0.0),
                              ez = fmax(fabs(rz) - hz, 0.0);
-                far = ex * ex + ey * ey + ez * ez >= far2;
+                const double d2 = ex * ex + ey * ey + ez * ez;
+                far = d2 >= far2;
+                cell = d2 < drop2;
             }
             const uint64_t mn = __ballot(cell && !far), mf = __ballot(cell && far);
             if (cell) {
@@ -311,22 +325,39 @@ __global__ __launch_bounds__(64) void k_quadrupole(const int32_t* __restrict__ g
                 b.w = (T)s[3];
                 d.x = (T)s[4];
                 d.y = (T)s[5];
-                cp[pos] = a;
-                cs1[pos] = b;
-                cs2[pos] = d;
+                sh.cp[pos] = a;
+                sh.cs1[pos] = b;
+                sh.cs2[pos] = d;
             }
             nnear += __popcll(mn);
             nfar += __popcll(mf);
         }
-        __syncthreads();
+        lds_order();
         T ox = 0, oy = 0, oz = 0;
+#pragma unroll 2
         for (int k = 0; k < nnear; ++k)
-            quad_pair<T, V4, V2, true>(cp[k], cs1[k], cs2[k], xi, yi, zi, cq, ox, oy, oz);
+            quad_pair<T, V4, V2, true>(sh.cp[k], sh.cs1[k], sh.cs2[k], xi, yi, zi, cq, ox, oy, oz);
+#pragma unroll 2
         for (int k = kQChunk - nfar; k < kQChunk; ++k)
-            quad_pair<T, V4, V2, false>(cp[k], cs1[k], cs2[k], xi, yi, zi, cq, ox, oy, oz);
+            quad_pair<T, V4, V2, false>(sh.cp[k], sh.cs1[k], sh.cs2[k], xi, yi, zi, cq, ox, oy, oz);
         sx += (double)ox;
         sy += (double)oy;
         sz += (double)oz;
+    }
+    if (W > 1) {   // each wave's totals in its own cells' place
+        lds_order();
+        double* mine = reinterpret_cast<double*>(sh.cp) + lane * 3;
+        mine[0] = sx;
+        mine[1] = sy;
+        mine[2] = sz;
+        __syncthreads();
+        if (wave != 0) return;
+        for (int w = 1; w < W; ++w) {
+            const double* r = reinterpret_cast<const double*>(sh_all[w].cp) + lane * 3;
+            sx += r[0];
+            sy += r[1];
+            sz += r[2];
+        }
     }
     if (lane < cnt) {
         const int64_t o = (int64_t)perm[me] * os;
@@ -351,18 +382,19 @@ void launch_quadrupole(const Tree& t, const Lists& l, const srf_params& p, doubl
     hipLaunchKernelGGL(k_second_moments, dim3((unsigned)((nn + 63) / 64)), dim3(64), 0, st, nn, t.range.get(), used.get(),
                        t.px.get(), t.py.get(), t.pz.get(), t.pm.get(), t.nX.get(), t.nY.get(), t.nZ.get(), S.get());
     SRF_HIP(hipGetLastError());
-    const unsigned ng = (unsigned)t.n_groups;
-    if (p.precision == SRF_FP64) {
-        hipLaunchKernelGGL(k_quadrupole<double>, dim3(ng), dim3(64), 0, st, t.gfirst.get(), t.gcount.get(),
-                           t.glo.get(), t.ghi.get(), l.off.get(), l.ent.get(), t.perm.get(), t.px.get(), t.py.get(),
-                           t.pz.get(), t.nX.get(), t.nY.get(), t.nZ.get(), S.get(),
-                           make_qcoef<double>(p.r_cut, p.eps), 0.25 * p.r_cut * p.r_cut, p.G, ax, ay, az, os);
-    } else {
-        hipLaunchKernelGGL(k_quadrupole<float>, dim3(ng), dim3(64), 0, st, t.gfirst.get(), t.gcount.get(),
-                           t.glo.get(), t.ghi.get(), l.off.get(), l.ent.get(), t.perm.get(), t.px.get(), t.py.get(),
-                           t.pz.get(), t.nX.get(), t.nY.get(), t.nZ.get(), S.get(),
-                           make_qcoef<float>(p.r_cut, p.eps), 0.25 * p.r_cut * p.r_cut, p.G, ax, ay, az, os);
-    }
+    const int64_t ng = t.n_groups;
+    with_waves(ng, [&](auto waves) {
+        constexpr int W = decltype(waves)::value;
+        auto run = [&](auto coef, auto kernel, int w) {
+            hipLaunchKernelGGL(kernel, dim3((unsigned)ng), dim3(64 * w), 0, st, t.gfirst.get(), t.gcount.get(),
+                               t.glo.get(), t.ghi.get(), l.off.get(), l.ent.get(), t.perm.get(), t.px.get(),
+                               t.py.get(), t.pz.get(), t.nX.get(), t.nY.get(), t.nZ.get(), S.get(), coef,
+                               0.25 * p.r_cut * p.r_cut, p.G, ax, ay, az, os);
+        };
+        constexpr int WD = W < 4 ? W : 4;   // a CU's LDS holds eight FP64 waves either way
+        if (p.precision == SRF_FP64) run(make_qcoef<double>(p.r_cut, p.eps), k_quadrupole<double, WD>, WD);
+        else run(make_qcoef<float>(p.r_cut, p.eps), k_quadrupole<float, W>, W);
+    });
     SRF_HIP(hipGetLastError());
 }
 
