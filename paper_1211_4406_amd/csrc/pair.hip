@@ -7,7 +7,8 @@
 // mass.  (In trees of few groups several waves share a group, each with
 // tiles, or chunks of them, of its own.)  With N_i particles in the group, the wave runs S = floor(64/N_i)
 // independent j-streams (lane = i + N_i * stream), whose FP64 partial sums
-// are added at the end.  Each staged tile is split into near entries (some
+// are added at the end; the force's lanes take (chunk, target) pairs instead
+// where N_i is 33 to 50.  Each staged tile is split into near entries (some
 // target may lie within r_cut/2 of them) and far entries (none can); far
 // pairs take only the [1,2] form of the cutoff function.
 //
@@ -254,10 +255,18 @@ __device__ __forceinline__ V4 load_entry_d2(int32_t v, const Src& s, double cx, 
 // are exactly zero, and the chunks are those of the whole tile, so that the
 // sums are the same (force kernel 13.1 -> 12.8 ms on the 2^24 lattice, where
 // 15% of the far entries go, and 10.7 -> 9.8 ms on the 1.3e7 clustered set);
-// far_n[c] is the number of entries left in chunk c, and the entries past the last whole round of U of the unrolled loop, which form
-// a sum of their own, are chunk kTail.
+// far_n[c] is the number of entries left in chunk c; the entries past the last
+// whole round of U of the unrolled loop, which form a sum of their own, are
+// chunk kTail.
 constexpr int kFlush = 32;
 constexpr int kTail = kTile / kFlush;
+// Groups of 33 to this many targets take (chunk, target) pairs per lane
+// (force_flat), larger ones a target per lane: at 50 of 64 lanes the rounds'
+// own work (about 40 instructions for 32 pairs' 700 to 1000) is repaid.  Force
+// kernel at limits 0 / 42 / 46 / 50 / 54 / 58: 2435 / 2349 / 2327 / 2324 / 2321 /
+// 2360 us (2^21 clustered), 9.49 / 9.19 / 9.15 / 9.17 / 9.17 / 9.2 ms (1.3e7
+// clustered), 831 / 804 / 806 / 806 / 806 us (2^20 uniform).
+constexpr int kFlatTargets = 50;
 
 template <class V4>
 struct TileShared {
@@ -278,7 +287,8 @@ __device__ __forceinline__ TileCount stage_tile(const int32_t* __restrict__ ent,
     const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
     if (DROP && lane <= kTail) sh.far_n[lane] = 0;
     V4 e[kSub];
-    int32_t id[kSub], kf[kSub], kr[kSub];   // row; place among the far entries, and among those kept (-1: near or dropped)
+    // row; place among the far entries, and among those kept (-1: near or dropped)
+    int32_t id[kSub], kf[kSub], kr[kSub];
     int nnear = 0, nfar = 0, nkept = 0;
 #pragma unroll
     for (int j = 0; j < kSub; ++j) {
@@ -390,6 +400,71 @@ __device__ __forceinline__ void force_far_chunks(const TileShared<V4>& sh, int a
     }
 }
 
+// The same chunks for a group of 33 to kFlatTargets targets, where a wave with
+// a lane per target would leave up to half of its lanes idle: the (chunk,
+// target) pairs are numbered through, chunks longest first, and each round
+// gives 64 of them to the lanes.  Lane q holds chunk q's first entry `at` and
+// length n (at most 18 chunks); x, y, z is target `lane`.  After a round each
+// target's one or two partial sums move to its lane.  INV = ceil(2^16 / cnt)
+// divides task numbers below 1100 by cnt exactly.
+template <class T, class V4, bool NEAR, bool RS>
+__device__ __forceinline__ void force_flat(const V4* tile, int at, int n, int chunks, int cnt, int inv, int lane,
+                                           int sub, int subs, T x, T y, T z, const Coef<T>& c, double& sx,
+                                           double& sy, double& sz) {
+    constexpr int U = NEAR ? 4 : 8;
+    const int tasks = chunks * cnt;
+    for (int t0 = 64 * sub; t0 < tasks; t0 += 64 * subs) {
+        const int task = t0 + lane, q = (task * inv) >> 16, i = task - q * cnt;
+        const V4* tp = tile + __shfl(at, q, 64);
+        const int nq = __shfl(n, q, 64);   // (by all lanes: lane q may have no task itself)
+        const T xi = __shfl(x, i, 64), yi = __shfl(y, i, 64), zi = __shfl(z, i, 64);
+        int left = task < tasks ? nq : 0;
+        Acc<T, false> acc;
+        for (; left >= U; left -= U, tp += U) {
+            V4 pp[U];
+#pragma unroll
+            for (int k = 0; k < U; ++k) pp[k] = tp[k];
+#pragma unroll
+            for (int k = 0; k < U; ++k) pair_force<T, V4, NEAR, false, RS>(pp[k], xi, yi, zi, c, acc);
+        }
+        for (; left > 0; --left, ++tp) pair_force<T, V4, NEAR, false, RS>(tp[0], xi, yi, zi, c, acc);
+        // the lane of target `lane`'s first task of this round, and of a second one
+        int a = lane - __builtin_amdgcn_readfirstlane(i);
+        if (a < 0) a += cnt;
+        const int b = a + cnt;
+        const T ax = __shfl(acc.x, a, 64), ay = __shfl(acc.y, a, 64), az = __shfl(acc.z, a, 64);
+        const T bx = __shfl(acc.x, b, 64), by = __shfl(acc.y, b, 64), bz = __shfl(acc.z, b, 64);
+        sx += kGScale * ((double)ax + (b < 64 ? (double)bx : 0.0));
+        sy += kGScale * ((double)ay + (b < 64 ? (double)by : 0.0));
+        sz += kGScale * ((double)az + (b < 64 ? (double)bz : 0.0));
+    }
+}
+
+// A tile's near and far chunks by force_flat.  The near chunks are those of
+// force_segment, the far ones (sorted by their lengths) those of stage_tile.
+template <class T, class V4, bool RS>
+__device__ __forceinline__ void force_flat_tile(const TileShared<V4>& sh, TileCount tc, int cnt, int inv, int lane,
+                                                int sub, int subs, T x, T y, T z, const Coef<T>& c, double& sx,
+                                                double& sy, double& sz) {
+    const int even = tc.near / 4 * 4, full = even / kFlush, part = even % kFlush, tail = tc.near - even;
+    const bool in_part = lane == full && part > 0;
+    const int near_at = lane < full || in_part ? kFlush * lane : even;
+    const int near_n = lane < full ? kFlush : in_part ? part : tail;
+    force_flat<T, V4, true, RS>(sh.tile, near_at, near_n, full + (part > 0) + (tail > 0), cnt, inv, lane, sub, subs, x,
+                                y, z, c, sx, sy, sz);
+    const int far_n = lane <= kTail ? sh.far_n[lane] : 0;
+    const int far_at = tc.near + wave_scan(far_n) - far_n;
+    int rank = 0;
+#pragma unroll
+    for (int j = 0; j <= kTail; ++j) {
+        const int nj = __builtin_amdgcn_readlane(far_n, j);
+        rank += nj > far_n || (nj == far_n && j < lane);
+    }
+    const int sorted = __builtin_amdgcn_ds_permute(4 * rank, far_at << 8 | far_n);
+    force_flat<T, V4, false, RS>(sh.tile, sorted >> 8, sorted & 255, __popcll(__ballot(far_n > 0)), cnt, inv, lane, sub,
+                                 subs, x, y, z, c, sx, sy, sz);
+}
+
 struct GroupArgs {
     const int32_t *gfirst, *gcount;
     const double *glo, *ghi;
@@ -419,7 +494,7 @@ __device__ __forceinline__ Deal deal_tiles(int64_t entries, int wave) {
 }
 
 // ------------------------------------------------------------------ force
-template <class T, int S, int W, bool COMP, bool RS>
+template <class T, int S, int W, bool FLAT, bool COMP, bool RS>
 __device__ __forceinline__ void force_group(const GroupArgs& ga, const Src& src, const Coef<T>& c0, double G,
                                             double* __restrict__ ax, double* __restrict__ ay,
                                             double* __restrict__ az, int64_t os, int64_t g, int32_t first,
@@ -442,6 +517,7 @@ __device__ __forceinline__ void force_group(const GroupArgs& ga, const Src& src,
     const T xi = (T)image(src.px[me] - cx), yi = (T)image(src.py[me] - cy), zi = (T)image(src.pz[me] - cz);
     double sx = 0, sy = 0, sz = 0;
     const int64_t e0 = ga.off[g], e1 = ga.off[g + 1];
+    const int inv = FLAT ? (65535 + cnt) / cnt : 0;
     const Deal deal = deal_tiles<W>(e1 - e0, wave);
     for (int64_t tb = e0 + deal.tile * kTile; tb < e1; tb += deal.step * kTile) {
         const int len = (int)((e1 - tb) < kTile ? (e1 - tb) : kTile);
@@ -449,6 +525,10 @@ __device__ __forceinline__ void force_group(const GroupArgs& ga, const Src& src,
         const TileCount tc = stage_tile<T, V4, S == 1, 8>(ga.ent + tb, len, lane, src, cx, cy, cz, hx, hy, hz,
                                                           c0.far2, drop2, sh, nullptr, 0);
         lds_order();
+        if (FLAT) {
+            force_flat_tile<T, V4, RS>(sh, tc, cnt, inv, lane, deal.sub, deal.subs, xi, yi, zi, c, sx, sy, sz);
+            continue;
+        }
         if (active) {
             force_segment<T, V4, S, true, COMP, RS>(sh.tile, 0, tc.near, st, deal.sub, deal.subs, xi, yi, zi, c, sx,
                                                     sy, sz);
@@ -492,11 +572,13 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(sizeof(T
     __shared__ double red[64 * W * 3];
     const int64_t g = xcd_block(blockIdx.x, gridDim.x);
     const int32_t first = ga.gfirst[g], cnt = ga.gcount[g];
-    if (cnt > 32) force_group<T, 1, W, COMP, RS>(ga, src, c, G, ax, ay, az, os, g, first, cnt, sh, red);
-    else if (cnt > 21) force_group<T, 2, W, COMP, RS>(ga, src, c, G, ax, ay, az, os, g, first, cnt, sh, red);
-    else if (cnt > 16) force_group<T, 3, W, COMP, RS>(ga, src, c, G, ax, ay, az, os, g, first, cnt, sh, red);
-    else if (cnt > 8) force_group<T, 4, W, COMP, RS>(ga, src, c, G, ax, ay, az, os, g, first, cnt, sh, red);
-    else force_group<T, 8, W, COMP, RS>(ga, src, c, G, ax, ay, az, os, g, first, cnt, sh, red);
+    if (cnt > (COMP ? 32 : kFlatTargets))
+        force_group<T, 1, W, false, COMP, RS>(ga, src, c, G, ax, ay, az, os, g, first, cnt, sh, red);
+    else if (cnt > 32) force_group<T, 1, W, !COMP, COMP, RS>(ga, src, c, G, ax, ay, az, os, g, first, cnt, sh, red);
+    else if (cnt > 21) force_group<T, 2, W, false, COMP, RS>(ga, src, c, G, ax, ay, az, os, g, first, cnt, sh, red);
+    else if (cnt > 16) force_group<T, 3, W, false, COMP, RS>(ga, src, c, G, ax, ay, az, os, g, first, cnt, sh, red);
+    else if (cnt > 8) force_group<T, 4, W, false, COMP, RS>(ga, src, c, G, ax, ay, az, os, g, first, cnt, sh, red);
+    else force_group<T, 8, W, false, COMP, RS>(ga, src, c, G, ax, ay, az, os, g, first, cnt, sh, red);
 }
 
 // -------------------------------------------------------------- potential

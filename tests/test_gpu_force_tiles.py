@@ -42,3 +42,26 @@ def test_force_of_tiles(n_group, r_cut, eps, refit):
         a = srf.short_range_force(tree, lists, q).cpu().numpy()
         check(a, a_ref, ref.force_bound(U64 if fp64 else U32), constant("force", fp64, max_list(ref)),
               f"force fp64={fp64} compensated={comp}")
+
+
+@pytest.mark.parametrize("n_group", [34, 43, 50, 51])
+@pytest.mark.parametrize("r_cut", [0.004, 0.03, 0.24])
+@pytest.mark.parametrize("n", [49, 130, 2357])
+def test_force_of_numbered_pairs_of_chunks_and_targets(n_group, r_cut, n):
+    """Groups of 33 to 50 targets take the lanes by (chunk, target) pairs: lists from one short chunk
+    to several tiles, and last rounds of fewer pairs than there are chunks."""
+    rng = np.random.default_rng(4700 + n_group + n)
+    pos = np.mod(0.5 + 0.04 * rng.standard_normal((n, 3)), 1.0)
+    params = synth.Params(1.0, r_cut, 1e-3, 0.5, n_group, 8)
+    print(f"[gpu] force pairs n={n} n_group={n_group} r_cut={r_cut}", flush=True)
+    m = rng.uniform(0.5, 1.5, n) / n
+    ref = oracle.OracleTree(pos[:, 0].copy(), pos[:, 1].copy(), pos[:, 2].copy(), m, params)
+    p = srf.Params.of(params)
+    tree = srf.tree_build(torch.tensor(pos, device="cuda"), torch.tensor(m, device="cuda"), p)
+    lists = srf.make_lists(tree, p)
+    a_ref = ref.force()
+    for fp64 in (False, True):
+        q = dataclasses.replace(p, precision=srf.FP64 if fp64 else srf.FP32_REL)
+        a = srf.short_range_force(tree, lists, q).cpu().numpy()
+        check(a, a_ref, ref.force_bound(U64 if fp64 else U32), constant("force", fp64, max_list(ref)),
+              f"force fp64={fp64}")
