@@ -41,7 +41,7 @@ METRIC = "short-range pair interactions/s + % FP32 VALU peak; fwd and fwd+adjoin
 # rocprofv3 counter runs, summarised in this file; they are used only while
 # the kernel sources still hash to the value recorded with them.
 COUNTER_PROFILE = os.path.join(ROOT, "profiles", "pair_kernels_zeldovich256_counters.md")
-KERNEL_SOURCES = ("paper_1211_4406_amd/csrc/pair.hip", "paper_1211_4406_amd/csrc/common.h")
+KERNEL_SOURCES = tuple(f"paper_1211_4406_amd/csrc/{f}" for f in ("pair.hip", "group.h", "common.h"))
 
 
 def kernel_source_hash() -> str:
@@ -399,9 +399,11 @@ def main():
     achieved = fpi * I / (kd * 1e-3)
     prof = profiled_counters(args.workload, ps.params.theta)
     # kernel instances the library launches for these parameters: plain FP32
-    # partial sums; far pairs take r from s when (2 eps / r_cut)^2 <= 5e-4
+    # partial sums; far pairs take r from s when (2 eps / r_cut)^2 <= 5e-4;
+    # waves per group by the number of groups
     rs = "true" if 4.0 * ps.params.eps ** 2 / ps.params.r_cut ** 2 <= 5e-4 else "false"
-    kernel_names = {"force": f"k_force<float, false, {rs}>", "adjoint": f"k_adjoint<float, {rs}>"}
+    waves = 1 if info["n_groups"] >= 55000 else 4 if info["n_groups"] >= 3500 else 8
+    kernel_names = {"force": f"k_force<float, {waves}, false, {rs}>", "adjoint": f"k_adjoint<float, {rs}, {waves}>"}
     kname = kernel_names[dominant]
     traffic = None
     executed = {}

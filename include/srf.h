@@ -113,7 +113,9 @@ typedef struct srf_lists srf_lists;
  *   out:        (host) receives the new handle.
  * The inputs are copied; they may be reused once `stream` passes this call.
  * Synchronises `stream` once (to read the number of cells and groups and
- * the device's check of the inputs).  Part of the work runs on a second,
+ * the device's check of the inputs); a second time when more than 1024
+ * particles share a cube of side 2^-10 (the sort is then repeated on the
+ * whole keys).  Above 2^21 particles part of the work runs on a second,
  * library-owned stream of the same device (created on first use, default
  * priority); `stream` waits for it before this call returns, so work
  * queued on `stream` afterwards sees the whole tree.
@@ -162,8 +164,9 @@ int srf_tree_refit(srf_tree* t, const double* x, const double* y, const double* 
  * p must carry the n_group and n_leaf the tree was built with.  The lists
  * belong to this tree: after it is freed they are refused (SRF_EMISMATCH)
  * by every call, even with a new tree at the same address.
- * Synchronises `stream` once (to size the list buffer), twice when some
- * group's list holds more than 2048 leaves and accepted cells.
+ * Synchronises `stream` once (to size the list buffer); up to three times
+ * when some group's list holds more leaves and accepted cells than its slot
+ * of the scratch memory (4096 in trees of up to 65536 groups, else 2048).
  * Errors: SRF_EINVAL, SRF_EMISMATCH, SRF_ENOMEM, SRF_EHIP. */
 int srf_make_lists(const srf_tree* t, const srf_params* p, void* stream, srf_lists** out);
 
@@ -259,7 +262,7 @@ int srf_short_range_potential(const srf_tree* t, const srf_lists* l, const srf_p
  * (not added) to (ax, ay, az)[i*out_stride] in input order; PP + PM is the
  * TreePM force.  Uses the sorted particles of `t`; r_cut and G need not
  * match the tree's lists, but r_cut is normally the one of the PP part.
- *   n_mesh: a power of two in [16, 1024] (memory: 40 n_mesh^3 bytes).
+ *   n_mesh: a power of two in [16, 1024] (memory: 48 n_mesh^3 bytes).
  * Asynchronous on `stream` (FP64 atomics: reproducible only to rounding).
  * Errors: SRF_EINVAL, SRF_ENOMEM, SRF_EHIP. */
 int srf_pm_force(const srf_tree* t, double G, double r_cut, int32_t n_mesh, double* ax, double* ay, double* az,
@@ -280,7 +283,8 @@ int srf_drift(int64_t n, double* x, double* y, double* z, int64_t x_stride, cons
 void srf_tree_free(srf_tree* t);
 void srf_lists_free(srf_lists* l);
 
-/* Return every cached device block to HIP (synchronises the device). */
+/* Return every cached device block, and the pinned host pieces that sizes are
+ * read through, to HIP (synchronises the device). */
 void srf_release_cache(void);
 
 const char* srf_strerror(int status);
