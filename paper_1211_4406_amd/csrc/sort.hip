@@ -148,10 +148,42 @@ __global__ __launch_bounds__(kThreads) void k_digit_scan(int64_t tiles, int32_t*
     if (tid == 0) dtot[blockIdx.x] = carry;
 }
 
-// Stable scatter of one tile.  Ranking: in each round the lanes holding the
-// same digit are found by eight ballots; a key's rank is its wave's running
-// count of that digit (an LDS counter, advanced by the lowest such lane)
-// plus the number of such lanes below it.  Tile position: digits in order,
+// A key's rank among its wave's keys of the same digit: in each round the lanes
+// holding the same digit are found by eight ballots; the rank is the wave's
+// running count of that digit (an LDS counter, advanced by the lowest such
+// lane) plus the number of such lanes below it.  Item r of a lane is a key if
+// 64 r < left.
+template <int ITEMS>
+__device__ __forceinline__ void wave_ranks(int64_t left, const uint32_t (&key)[ITEMS], int shift, int lane,
+                                           int32_t* wc, int32_t (&rank)[ITEMS]) {
+    const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) {
+        const bool valid = 64 * r < left;
+        const int d = (int)((key[r] >> shift) & 0xff);
+        // lanes holding the same digit (invalid lanes match only each other)
+        uint64_t peers = __ballot(valid);
+        if (!valid) peers = ~peers;
+#pragma unroll
+        for (int b = 0; b < 8; ++b) {
+            const bool bit = (d >> b) & 1;
+            const uint64_t bal = __ballot(bit);
+            peers &= bit ? bal : ~bal;
+        }
+        const int lower = __popcll(peers & lt);
+        int32_t old = 0;
+        if (valid) old = wc[d];
+        rank[r] = old + lower;
+        if (valid && lower == 0) wc[d] = old + __popcll(peers);
+        // the next round's reads must see this round's counter (one wave:
+        // LDS operations complete in order; this keeps the compiler's too)
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    }
+}
+
+// Stable scatter of one tile.  Ranking by wave_ranks.  Tile position: digits in order,
 // within a digit the waves in order, then the rank.  The tile is reordered
 // in LDS so that each digit's run is written contiguously.
 template <bool V2, int ITEMS, bool SELF>
@@ -185,7 +217,6 @@ __global__ __launch_bounds__(kThreads) void k_scatter(int64_t n, const uint32_t*
         digit_total = dtot[tid];
     }
     __syncthreads();
-    const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
     const int64_t wbase = blockIdx.x * (int64_t)kTile + wid * 64 * ITEMS + lane;
     uint32_t key[ITEMS], val2[ITEMS];
     int32_t val[ITEMS], rank[ITEMS];
@@ -196,30 +227,7 @@ __global__ __launch_bounds__(kThreads) void k_scatter(int64_t n, const uint32_t*
         val[r] = i < n ? vin[i] : 0;
         val2[r] = (V2 && i < n) ? v2in[i] : 0u;
     }
-#pragma unroll
-    for (int r = 0; r < ITEMS; ++r) {
-        const bool valid = wbase + 64 * r < n;
-        const int d = (int)((key[r] >> shift) & 0xff);
-        // lanes holding the same digit (invalid lanes match only each other)
-        uint64_t peers = __ballot(valid);
-        if (!valid) peers = ~peers;
-#pragma unroll
-        for (int b = 0; b < 8; ++b) {
-            const bool bit = (d >> b) & 1;
-            const uint64_t bal = __ballot(bit);
-            peers &= bit ? bal : ~bal;
-        }
-        const int lower = __popcll(peers & lt);
-        int32_t old = 0;
-        if (valid) old = wc[wid][d];
-        rank[r] = old + lower;
-        if (valid && lower == 0) wc[wid][d] = old + __popcll(peers);
-        // the next round's reads must see this round's counter (one wave:
-        // LDS operations complete in order; this keeps the compiler's too)
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    }
+    wave_ranks<ITEMS>(n - wbase, key, shift, lane, wc[wid], rank);
     __syncthreads();
     // per digit (one per thread): the waves' exclusive prefix and the tile
     // total, then exclusive scans over digits of the tile totals and of the
@@ -283,6 +291,81 @@ __global__ __launch_bounds__(kThreads) void k_scatter(int64_t n, const uint32_t*
                 if (V2) v2out[dst] = sval2[p];
             }
         }
+    }
+}
+
+// The four passes of at most kBlockKeys keys by one workgroup, keys and indices
+// moving through LDS: one launch instead of eight, each of which is a few us of
+// latency.  khi is sorted in place; perm receives the order.  A pass is a chain
+// of ballots and LDS counters whose length is the keys per thread, so that past
+// 4096 keys other CUs' help is worth the launches: whole forward pass with the
+// passes by eight launches / by this kernel, us: 4096 particles 180-205 / 160,
+// 4100 (8 keys per thread here) 206-216 / 202, 8000 211-217 / 212, 12000 (16
+// keys) 262-269 / 287, 16384 277-287 / 312.
+constexpr int kBlockItems = 4;
+constexpr int kBlockWaves = 16;
+constexpr int64_t kBlockKeys = 64 * kBlockWaves * kBlockItems;
+__global__ __launch_bounds__(64 * kBlockWaves) void k_sort_block(int n, uint32_t* __restrict__ khi,
+                                                                 int32_t* __restrict__ perm) {
+    __shared__ int32_t wc[kBlockWaves][kDigits];   // running counts, then the places of the wave's first keys
+    __shared__ int32_t wsum[kDigits / 64];
+    __shared__ uint32_t skey[kBlockKeys];
+    __shared__ int32_t sval[kBlockKeys];
+    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+    const int base = wid * 64 * kBlockItems + lane;
+    uint32_t key[kBlockItems];
+    int32_t val[kBlockItems], rank[kBlockItems];
+#pragma unroll
+    for (int r = 0; r < kBlockItems; ++r) {
+        val[r] = base + 64 * r;
+        key[r] = val[r] < n ? khi[val[r]] : 0u;
+    }
+    for (int shift = 0; shift < 32; shift += 8) {
+        for (int k = tid; k < kBlockWaves * kDigits; k += 64 * kBlockWaves) (&wc[0][0])[k] = 0;
+        __syncthreads();
+        wave_ranks<kBlockItems>(n - base, key, shift, lane, wc[wid], rank);
+        __syncthreads();
+        // a digit per thread: the waves' exclusive prefix, and its scan over the digits
+        int32_t tot = 0, incl = 0;
+        if (tid < kDigits) {
+#pragma unroll
+            for (int w = 0; w < kBlockWaves; ++w) {
+                const int32_t c = wc[w][tid];
+                wc[w][tid] = tot;
+                tot += c;
+            }
+            incl = wave_scan(tot);
+            if (lane == 63) wsum[wid] = incl;
+        }
+        __syncthreads();
+        if (tid < kDigits) {
+            int32_t off = incl - tot;
+            for (int w = 0; w < wid; ++w) off += wsum[w];
+#pragma unroll
+            for (int w = 0; w < kBlockWaves; ++w) wc[w][tid] += off;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < kBlockItems; ++r) {
+            if (base + 64 * r >= n) continue;
+            const int at = wc[wid][(key[r] >> shift) & 0xff] + rank[r];   // < n, the counts' sum
+            skey[at] = key[r];
+            sval[at] = val[r];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < kBlockItems; ++r) {
+            if (base + 64 * r >= n) continue;
+            key[r] = skey[base + 64 * r];
+            val[r] = sval[base + 64 * r];
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < kBlockItems; ++r) {
+        const int i = base + 64 * r;
+        if (i >= n) continue;
+        khi[i] = key[r];
+        perm[i] = val[r];
     }
 }
 
@@ -572,7 +655,12 @@ void build_sorted(Tree& t, const double* x, const double* y, const double* z, in
             pass(8 * (p + 1), kb.get(), ka.get(), vb.get(), t.perm.get(), hb.get(), ha.get());
         }
     }
-    for (int p = 0; p < 4; p += 2) {
+    const bool one_block = few && n <= kBlockKeys;
+    if (one_block) {
+        hipLaunchKernelGGL(k_sort_block, dim3(1), dim3(64 * kBlockWaves), 0, st, (int)n, ha.get(), t.perm.get());
+        SRF_HIP(hipGetLastError());
+    }
+    for (int p = 0; p < 4 && !one_block; p += 2) {
         pass(8 * p, ha.get(), hb.get(), t.perm.get(), vb.get(), nullptr, nullptr);
         pass(8 * (p + 1), hb.get(), ha.get(), vb.get(), t.perm.get(), nullptr, nullptr);
     }

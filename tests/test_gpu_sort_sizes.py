@@ -38,3 +38,24 @@ def test_sort_sizes(n, clump, strided):
     assert np.array_equal(ex["keys"], keys[perm]) and np.array_equal(ex["perm"], perm)
     xs, ms = tree.sorted_particles()
     assert np.array_equal(xs, pos[perm]) and np.array_equal(ms, m[perm])
+
+
+@pytest.mark.parametrize("n", [1023, 2049, 4095, 4096])
+@pytest.mark.parametrize("kind", ["uniform", "one key", "two keys", "descending"])
+def test_sort_by_one_workgroup(n, kind):
+    """Up to 4096 keys are sorted by one workgroup; 4097 and up are in test_sort_sizes."""
+    print(f"[gpu] sort by one workgroup n={n} {kind}", flush=True)
+    rng = np.random.default_rng(2900 + n)
+    pos = rng.random((n, 3))
+    if kind == "one key":
+        pos[:] = (5 + 0.5) / 2 ** 11 + (rng.random((n, 3)) - 0.5) * 2e-4
+    elif kind == "two keys":   # stable: ties stay in input order
+        pos = np.where(rng.random((n, 1)) < 0.5, 0.125, 0.875) * np.ones((1, 3))
+    elif kind == "descending":
+        pos = np.sort(pos, axis=0)[::-1].copy()
+    keys = oracle.morton_keys(pos[:, 0].copy(), pos[:, 1].copy(), pos[:, 2].copy())
+    keys = np.asarray(keys[0] if isinstance(keys, tuple) else keys).astype(np.uint64)
+    perm = np.argsort(keys, kind="stable")
+    m = rng.uniform(0.5, 1.5, n)
+    ex = srf.tree_build(torch.tensor(pos, device="cuda"), torch.tensor(m, device="cuda"), srf.Params()).export()
+    assert np.array_equal(ex["keys"], keys[perm]) and np.array_equal(ex["perm"], perm)
