@@ -232,16 +232,18 @@ __device__ __forceinline__ int64_t xcd_block(int64_t b, int64_t nb) {
     return (x < r ? x * (q + 1) : r * (q + 1) + (x - r) * q) + y;
 }
 
-// x^(-1/2) in FP64 for x > 0: the hardware's estimate (about 2^-24 relative)
+// x^(-1/2) in FP64 for x >= 0: the hardware's estimate (about 2^-24 relative)
 // and one third-order step, y (1 + e/2 + 3 e^2/8) with e = 1 - x y^2, whose
 // remainder (5/16 e^3) is below 2^-66: the result is rounded about once, where
-// a correctly rounded square root and division round twice, for eight
-// instructions in place of some thirty.  x = 0 gives NaN, as 0 * inf does in
-// what it is used in.
+// a correctly rounded square root and division round twice, for nine
+// instructions in place of some thirty.  For x = 0 and x = inf, whose estimates
+// inf and 0 are the results, e is NaN: the minimum, far above any other e,
+// takes its place (the minimum of a NaN and a number is the number), and the
+// step leaves 0 and inf as they are.
 __device__ __forceinline__ double rsqrt64(double x) {
     const double y = __builtin_amdgcn_rsq(x);
     const double t = x * y, tl = __builtin_fma(x, y, -t);   // x y to twice FP64
-    const double e = __builtin_fma(-tl, y, __builtin_fma(-t, y, 1.0));
+    const double e = fmin(__builtin_fma(-tl, y, __builtin_fma(-t, y, 1.0)), 0x1p-16);
     return __builtin_fma(y * e, __builtin_fma(0.375, e, 0.5), y);
 }
 // x^(1/2) for x >= 0 from the same estimate: s = x y, with half its residual
