@@ -41,7 +41,17 @@ METRIC = "short-range pair interactions/s + % FP32 VALU peak; fwd and fwd+adjoin
 # rocprofv3 counter runs, summarised in this file; they are used only while
 # the kernel sources still hash to the value recorded with them.
 COUNTER_PROFILE = os.path.join(ROOT, "profiles", "pair_kernels_zeldovich256_counters.md")
-KERNEL_SOURCES = tuple(f"paper_1211_4406_amd/csrc/{f}" for f in ("pair.hip", "group.h", "common.h"))
+KERNEL_SOURCES = tuple(f"paper_1211_4406_amd/csrc/{f}" for f in ("pair.hip", "group.h", "waves.h", "common.h"))
+
+
+def waves_per_group(info: dict, reach: float) -> int:
+    """The library's choice (csrc/waves.h) for lists of this info()."""
+    ng = info["n_groups"]
+    mean = (info["n_particle_entries"] + info["n_node_entries"]) / ng
+    pairs = info["interactions"] / (64.0 * ng)
+    if ng <= 3000 and pairs >= 90.0:
+        return 8 if ng <= 700 else 4
+    return 4 if mean >= 700.0 and ng <= reach * mean else 1
 
 
 def kernel_source_hash() -> str:
@@ -400,10 +410,10 @@ def main():
     prof = profiled_counters(args.workload, ps.params.theta)
     # kernel instances the library launches for these parameters: plain FP32
     # partial sums; far pairs take r from s when (2 eps / r_cut)^2 <= 5e-4;
-    # waves per group by the number of groups
+    # waves per group by the groups and their lists (csrc/waves.h)
     rs = "true" if 4.0 * ps.params.eps ** 2 / ps.params.r_cut ** 2 <= 5e-4 else "false"
-    waves = 1 if info["n_groups"] >= 55000 else 4 if info["n_groups"] >= 3500 else 8
-    kernel_names = {"force": f"k_force<float, {waves}, false, {rs}>", "adjoint": f"k_adjoint<float, {rs}, {waves}>"}
+    kernel_names = {"force": f"k_force<float, {waves_per_group(info, 26.0)}, false, {rs}>",
+                    "adjoint": f"k_adjoint<float, {rs}, {waves_per_group(info, 16.0)}>"}
     kname = kernel_names[dominant]
     traffic = None
     executed = {}

@@ -5,6 +5,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "waves.h"
 
 namespace srf {
 
@@ -25,27 +26,12 @@ __device__ __forceinline__ void lds_order() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Waves per group.  A tree of few groups leaves SIMDs idle, or waiting for
-// its longest list, with one wave each; one of many fills the chip either way,
-// and waves of one block wait for each other at its end.  Kernel times with 1
-// / 4 / 8 waves, us (clustered sets unless said otherwise):
-//   groups           force                adjoint
-//   240              218 / - / 42         446 / 132 / 89
-//   1550             290 / 137 / 137      601 / 283 / 272
-//   3050             516 / 234 / 218      1106 / 435 / 435
-//   4200 (lattice)   307 / 265 / 281      571 / 503 / 550
-//   25000            1468 / 1367 / 1533   2440 / 2340 / 2790
-//   51000            2523 / 2476 / 2883   4839 / 4738 / 5809
-//   65000 (lattice)  4212 / 4284 / 5074   8120 / 8433 / 10070
-//   316000           9841 / 11004 / 14024
-constexpr int64_t kOneWaveGroups = 55000;
-constexpr int64_t kFourWaveGroups = 3500;
-
-// Calls f with the number of waves per group for ng groups.
+// Calls f with the number of waves per group for these lists.
 template <class F>
-void with_waves(int64_t ng, F&& f) {
-    if (ng >= kOneWaveGroups) f(std::integral_constant<int, 1>{});
-    else if (ng >= kFourWaveGroups) f(std::integral_constant<int, 4>{});
+void with_waves(const Lists& l, double reach, F&& f) {
+    const int w = waves_per_group(l.n_groups, l.n_entries, l.interactions, reach);
+    if (w == 1) f(std::integral_constant<int, 1>{});
+    else if (w == 4) f(std::integral_constant<int, 4>{});
     else f(std::integral_constant<int, 8>{});
 }
 

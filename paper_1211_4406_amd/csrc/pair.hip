@@ -1326,7 +1326,7 @@ void launch_force(const Tree& t, const Lists& l, const srf_params& p, double* ax
                   hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
     const int64_t ng = t.n_groups;
     if (ev0) SRF_HIP(hipEventRecord(ev0, st));
-    with_waves(ng, [&](auto waves) {
+    with_waves(l, kForceReach, [&](auto waves) {
         constexpr int W = decltype(waves)::value;
         auto run = [&](auto coef, auto kernel) {
             hipLaunchKernelGGL(kernel, dim3((unsigned)ng), dim3(64 * W), 0, st, group_args(t, l), src_args(t), coef,
@@ -1346,7 +1346,7 @@ void launch_force(const Tree& t, const Lists& l, const srf_params& p, double* ax
 
 void launch_potential(const Tree& t, const Lists& l, const srf_params& p, double* phi, int64_t os, hipStream_t st) {
     const int64_t ng = t.n_groups;
-    with_waves(ng, [&](auto waves) {
+    with_waves(l, kForceReach, [&](auto waves) {
         constexpr int W = decltype(waves)::value;
         auto run = [&](auto coef, auto kernel) {
             hipLaunchKernelGGL(kernel, dim3((unsigned)ng), dim3(64 * W), 0, st, group_args(t, l), src_args(t), coef,
@@ -1392,7 +1392,7 @@ static void adjoint_on(const Tree& t, const Lists& l, const srf_params& p, const
     double* sb = saz + nn;
     fill_f64(o.gj, 0.0, 4 * (n + nn), st);
     if (ev0) SRF_HIP(hipEventRecord(ev0, st));
-    with_waves(ng, [&](auto waves) {
+    with_waves(l, kAdjointReach, [&](auto waves) {
         constexpr int W = decltype(waves)::value;
         auto run = [&](auto coef, auto kernel) {
             hipLaunchKernelGGL(kernel, dim3((unsigned)ng), dim3(64 * W), 0, st, group_args(t, l), src_args(t), coef,

@@ -383,7 +383,7 @@ void launch_quadrupole(const Tree& t, const Lists& l, const srf_params& p, doubl
                        t.px.get(), t.py.get(), t.pz.get(), t.pm.get(), t.nX.get(), t.nY.get(), t.nZ.get(), S.get());
     SRF_HIP(hipGetLastError());
     const int64_t ng = t.n_groups;
-    with_waves(ng, [&](auto waves) {
+    with_waves(l, kQuadrupoleReach, [&](auto waves) {
         constexpr int W = decltype(waves)::value;
         auto run = [&](auto coef, auto kernel, int w) {
             hipLaunchKernelGGL(kernel, dim3((unsigned)ng), dim3(64 * w), 0, st, t.gfirst.get(), t.gcount.get(),
