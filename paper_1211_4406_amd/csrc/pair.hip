@@ -283,13 +283,41 @@ __device__ __forceinline__ TileCount stage_tile(const int32_t* __restrict__ ent,
                                                 double cx, double cy, double cz, double hx, double hy, double hz,
                                                 double far2, double drop2, TileShared<V4>& sh, int32_t* ids,
                                                 int32_t n_part) {
-    constexpr int kSub = kTile / 64;
     const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    if (DROP && lane <= kTail) sh.far_n[lane] = 0;
+    int nnear = 0, nfar = 0;
+    // without DROP every entry's place is known as it is read, and a list of few
+    // entries is one round (400000 single-particle groups, force: 362 us, 386 in
+    // the rounds of a whole tile below)
+    if (!DROP) {
+        for (int k0 = 0; k0 < len; k0 += 64) {
+            const int k = k0 + lane;
+            const bool valid = k < len;
+            bool far = false;
+            V4 e;
+            int32_t v = 0;
+            if (valid) {
+                v = ent[k];
+                double d2;
+                e = load_entry_d2<T, V4>(v, src, cx, cy, cz, hx, hy, hz, d2);
+                far = d2 >= far2;
+            }
+            const uint64_t mn = __ballot(valid && !far), mf = __ballot(far);
+            if (valid) {
+                const int pos = far ? len - 1 - (nfar + __popcll(mf & lt)) : nnear + __popcll(mn & lt);
+                sh.tile[pos] = e;
+                if (ids) ids[pos] = v >= 0 ? v : n_part + (-v - 1);
+            }
+            nnear += __popcll(mn);
+            nfar += __popcll(mf);
+        }
+        return {nnear, len};
+    }
+    constexpr int kSub = kTile / 64;
+    if (lane <= kTail) sh.far_n[lane] = 0;
     V4 e[kSub];
     // row; place among the far entries, and among those kept (-1: near or dropped)
     int32_t id[kSub], kf[kSub], kr[kSub];
-    int nnear = 0, nfar = 0, nkept = 0;
+    int nkept = 0;
 #pragma unroll
     for (int j = 0; j < kSub; ++j) {
         const int k = 64 * j + lane;
@@ -303,9 +331,9 @@ __device__ __forceinline__ TileCount stage_tile(const int32_t* __restrict__ ent,
             e[j] = load_entry_d2<T, V4>(v, src, cx, cy, cz, hx, hy, hz, d2);
             if (ids) id[j] = v >= 0 ? v : n_part + (-v - 1);
             far = d2 >= far2;
-            keep = far && (!DROP || d2 < drop2);
+            keep = far && d2 < drop2;
         }
-        const uint64_t mn = __ballot(valid && !far), mf = __ballot(far), mk = DROP ? __ballot(keep) : mf;
+        const uint64_t mn = __ballot(valid && !far), mf = __ballot(far), mk = __ballot(keep);
         if (valid && !far) {
             const int pos = nnear + __popcll(mn & lt);
             sh.tile[pos] = e[j];
@@ -326,10 +354,8 @@ __device__ __forceinline__ TileCount stage_tile(const int32_t* __restrict__ ent,
         const int pos = all - 1 - kr[j];
         sh.tile[pos] = e[j];
         if (ids) ids[pos] = id[j];
-        if (DROP) {
-            const int q = nfar - 1 - kf[j];
-            atomicAdd(&sh.far_n[q < whole ? q / kFlush : kTail], 1);
-        }
+        const int q = nfar - 1 - kf[j];
+        atomicAdd(&sh.far_n[q < whole ? q / kFlush : kTail], 1);
     }
     return {nnear, all};
 }
@@ -653,14 +679,14 @@ __device__ __forceinline__ T pair_pot(const V4& p, T xi, T yi, T zi, const PotCo
     return p.w * q * rinv;
 }
 
-// n sources from p on (with their rows in id), S apart, one FP32 sum.
-template <class T, class V4, bool NEAR, bool RS>
+// n sources from p on (with their rows in id), S apart, one FP32 sum; U of them
+// are read together.
+template <class T, class V4, bool NEAR, bool RS, int U>
 __device__ __forceinline__ T potential_chunk(const V4* p, const int32_t* id, int n, int step, int32_t me, T xi, T yi,
                                              T zi, const PotCoef<T>& c) {
-    constexpr int U = 4;
     T acc = 0;
     int k = 0;
-    for (; k + U <= n; k += U, p += U * step, id += U * step) {
+    for (; U > 1 && k + U <= n; k += U, p += U * step, id += U * step) {
         V4 pp[U];
         bool self[U];
 #pragma unroll
@@ -676,7 +702,7 @@ __device__ __forceinline__ T potential_chunk(const V4* p, const int32_t* id, int
     return acc;
 }
 
-template <class T, int S, int W, bool RS>
+template <class T, int S, int W, bool RS, int U>
 __device__ __forceinline__ void potential_group(const GroupArgs& ga, const Src& src, const PotCoef<T>& c0, double G,
                                                 double* __restrict__ phi, int64_t os, int32_t n_part, int64_t g,
                                                 int32_t first, int32_t cnt,
@@ -713,7 +739,7 @@ __device__ __forceinline__ void potential_group(const GroupArgs& ga, const Src& 
             constexpr bool NEAR = decltype(near)::value;
             for (int k = a + deal.sub * kFlush * S; k < b; k += deal.subs * kFlush * S) {
                 const int left = b - k - st, n = left <= 0 ? 0 : (left + S - 1) / S;
-                sum += (double)potential_chunk<T, V4, NEAR, RS>(sh.tile + k + st, ids + k + st,
+                sum += (double)potential_chunk<T, V4, NEAR, RS, U>(sh.tile + k + st, ids + k + st,
                                                                n < kFlush ? n : kFlush, S, me, xi, yi, zi, c);
             }
         };
@@ -726,7 +752,7 @@ __device__ __forceinline__ void potential_group(const GroupArgs& ga, const Src& 
             const int end_c = tc.near + wave_scan(n_c);
             for (int u = deal.sub; u < kTail; u += deal.subs) {
                 const int n = __builtin_amdgcn_readlane(n_c, u), k = __builtin_amdgcn_readlane(end_c, u) - n;
-                sum += (double)potential_chunk<T, V4, false, RS>(sh.tile + k, ids + k, n, 1, me, xi, yi, zi, c);
+                sum += (double)potential_chunk<T, V4, false, RS, U>(sh.tile + k, ids + k, n, 1, me, xi, yi, zi, c);
             }
         }
     }
@@ -744,7 +770,12 @@ __device__ __forceinline__ void potential_group(const GroupArgs& ga, const Src& 
 
 // Streams per group as in the force kernel.  `n_part` is the particle count
 // (the staged rows of cells start there, so that no cell matches a target).
-template <class T, int W, bool RS>
+// NARROW is for trees whose groups hold at most 8 targets: without the other
+// paths, and with one source read at a time, seven waves fit a SIMD instead of
+// five, which short lists need (400000 single-particle groups with lists of 39
+// entries: 238 us, 278 in the other form; 33455 groups of 3 with 335: 111 and
+// 112; from 9 targets on the other form is the faster one).
+template <class T, int W, bool RS, bool NARROW>
 __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 1))) void k_potential(
     GroupArgs ga, Src src, PotCoef<T> c, double G, double* __restrict__ phi, int64_t os, int32_t n_part) {
     __shared__ TileShared<typename Vec4<T>::type> sh[W];
@@ -752,11 +783,15 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(sizeof(T
     __shared__ double red[64 * W];
     const int64_t g = xcd_block(blockIdx.x, gridDim.x);
     const int32_t first = ga.gfirst[g], cnt = ga.gcount[g];
-    if (cnt > 32) potential_group<T, 1, W, RS>(ga, src, c, G, phi, os, n_part, g, first, cnt, sh, ids, red);
-    else if (cnt > 21) potential_group<T, 2, W, RS>(ga, src, c, G, phi, os, n_part, g, first, cnt, sh, ids, red);
-    else if (cnt > 16) potential_group<T, 3, W, RS>(ga, src, c, G, phi, os, n_part, g, first, cnt, sh, ids, red);
-    else if (cnt > 8) potential_group<T, 4, W, RS>(ga, src, c, G, phi, os, n_part, g, first, cnt, sh, ids, red);
-    else potential_group<T, 8, W, RS>(ga, src, c, G, phi, os, n_part, g, first, cnt, sh, ids, red);
+    if constexpr (NARROW) {
+        potential_group<T, 8, W, RS, 1>(ga, src, c, G, phi, os, n_part, g, first, cnt, sh, ids, red);
+    } else {
+        if (cnt > 32) potential_group<T, 1, W, RS, 4>(ga, src, c, G, phi, os, n_part, g, first, cnt, sh, ids, red);
+        else if (cnt > 21) potential_group<T, 2, W, RS, 4>(ga, src, c, G, phi, os, n_part, g, first, cnt, sh, ids, red);
+        else if (cnt > 16) potential_group<T, 3, W, RS, 4>(ga, src, c, G, phi, os, n_part, g, first, cnt, sh, ids, red);
+        else if (cnt > 8) potential_group<T, 4, W, RS, 4>(ga, src, c, G, phi, os, n_part, g, first, cnt, sh, ids, red);
+        else potential_group<T, 8, W, RS, 4>(ga, src, c, G, phi, os, n_part, g, first, cnt, sh, ids, red);
+    }
 }
 
 // ---------------------------------------------------------------- adjoint
@@ -1352,9 +1387,15 @@ void launch_potential(const Tree& t, const Lists& l, const srf_params& p, double
             hipLaunchKernelGGL(kernel, dim3((unsigned)ng), dim3(64 * W), 0, st, group_args(t, l), src_args(t), coef,
                                p.G, phi, os, (int32_t)t.n);
         };
-        if (p.precision == SRF_FP64) run(make_pot_coef<double>(p.r_cut, p.eps), k_potential<double, W, false>);
-        else if (far_r_from_s(p)) run(make_pot_coef<float>(p.r_cut, p.eps), k_potential<float, W, true>);
-        else run(make_pot_coef<float>(p.r_cut, p.eps), k_potential<float, W, false>);
+        auto run_as = [&](auto narrow) {
+            constexpr bool N = decltype(narrow)::value;
+            const PotCoef<float> cf = make_pot_coef<float>(p.r_cut, p.eps);
+            if (p.precision == SRF_FP64) run(make_pot_coef<double>(p.r_cut, p.eps), k_potential<double, W, false, N>);
+            else if (far_r_from_s(p)) run(cf, k_potential<float, W, true, N>);
+            else run(cf, k_potential<float, W, false, N>);
+        };
+        if (W == 1 && t.n_group <= 8) run_as(std::bool_constant<W == 1>{});
+        else run_as(std::false_type{});
     });
     SRF_HIP(hipGetLastError());
 }
