@@ -137,12 +137,9 @@ constexpr uint32_t kWalkCountMax = 0x7fffffu;
 //   x = ix | (a & 0x7ff) << 21,  y = iy | ((a >> 11) & 0x7ff) << 21,
 //   z = iz | ((a >> 22) & 0x3ff) << 21,  w = level | children << 5,
 // a = the slot of the first child, or a leaf's (children = 0) particle count.
-// Trees whose lists are built by one wave per group (lists.hip): those of at
-// most kWaveWalkGroups groups, and up to kDeepWalkGroups in a tree deeper than
-// a uniform set's by kDeepLevels.
-constexpr int64_t kWaveWalkGroups = 3 << 16, kDeepWalkGroups = 1 << 20;
-constexpr int kDeepLevels = 4;
-constexpr int64_t kWaveWalkCells = 1 << 30;    // and of cells (items are sorted as 31-bit keys)
+// Trees whose lists may be built by one wave per group keep these (walks.h), up
+// to this many cells (items are sorted as 31-bit keys).
+constexpr int64_t kWaveWalkCells = 1 << 30;
 // A cell of a refitted tree for the list traversal, 32 bytes: the packed
 // record and its box rounded outward to multiples of q = 2^-(level + 10),
 // per axis a the 16-bit offsets (in q) of its lower and upper bound from
@@ -181,7 +178,7 @@ struct Tree {
     // particle; a cell's children are one run of the next level's slots):
     // first particle, preorder id and first child slot (-1 for a leaf)
     DevBuf<int32_t> sfirst, spre, schild;
-    DevBuf<uint4> srec;        // slot-ordered walk records (where the waves' walk is taken)
+    DevBuf<uint4> srec;        // slot-ordered walk records (where waves may walk the tree)
     DevBuf<double> clo, chi;   // [nn*3] boxes of the cells of a refitted tree
     DevBuf<RefitCell> rpack;   // their walk records
     // groups, in order of first

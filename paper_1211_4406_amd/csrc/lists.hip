@@ -34,6 +34,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "walks.h"
 
 namespace srf {
 namespace {
@@ -489,8 +490,8 @@ __global__ __launch_bounds__(kListThreads) void k_lists(int64_t ng, const double
     }
 }
 
-// The same lists from one wave per group (where the tree has the slot-ordered
-// records).  The wave keeps the cells its group still has to
+// The same lists from one wave per group (where walks.h says so).  The wave
+// keeps the cells its group still has to
 // look at on a stack in LDS, as level slots; it takes up to 64 of them at a
 // time, one per lane, and pushes the children of those it opens (they are
 // one run of the next level's slots, so their records are read side by
@@ -501,15 +502,12 @@ __global__ __launch_bounds__(kListThreads) void k_lists(int64_t ng, const double
 // A thread's walk is a chain of dependent loads, one per visited cell: about
 // 1.1 ms for a clustered set of any size below 10^6 particles, with a wave
 // for 64 groups and most of the chip idle.  Here the chain is one load per 64
-// cells, and the waves are 64 times as many.
-// It issues more instructions per group (idle lanes in the top levels, the
-// sort), so that a tree that fills the chip with threads' walks keeps those,
-// except a deep one, where the threads of a wave wait for the longest walk.
+// cells, and the waves are 64 times as many; but it issues more instructions
+// per group (idle lanes in the top levels, the sort).
 // k_lists against k_walk, us: 160 / 11 at 4096 uniform particles (96 groups),
 // 1117 / 49 at 131071 clustered ones (3050), 1564 / 383 at 2^21 (51000), 744
 // / 184 at 2^21 on the Zel'dovich lattice (33000), 1594 / 1317 at 1.3e7
-// clustered (316000, 14 levels), but 1214 / 1403 at 2^24 on the lattice
-// (265000, 9 levels); refitted trees at 2^21: 933 / 290.
+// clustered (316000, 14 levels); refitted trees at 2^21: 933 / 290.
 // In trees of at most kWideGroups groups a slot holds kWideSlot items (a group
 // of a void beside clumps of a 2 x 10^5 particle set has 2100), and a group of
 // more than kWaveItems leaves them unsorted for k_sort_wide, whose registers
@@ -853,7 +851,9 @@ void build_lists(const Tree& t, Lists& l, hipStream_t st) {
     l.n_groups = ng;
     l.off.alloc(ng + 1, st);
     DevBuf<int64_t> icnt(ng + 1, st);
-    const bool waves = ng > 0 && t.srec.get();
+    int32_t cells[kLevels];
+    for (int L = 0; L < kLevels; ++L) cells[L] = t.level_off[L + 1] - t.level_off[L];
+    const bool waves = ng > 0 && t.srec.get() && wave_walk(t.n, ng, cells, t.max_level, l.r_cut, l.theta);
     const int64_t slot_items = waves && ng <= kWideGroups ? kWideSlot : kSlot;
     DevBuf<int32_t> slots(ng > 0 ? ng * slot_items : 1, st);
     DevBuf<unsigned long long> totals(4 * kTotals, st);

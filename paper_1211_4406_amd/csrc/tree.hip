@@ -33,6 +33,7 @@
 #include <string>
 
 #include "common.h"
+#include "walks.h"
 
 namespace srf {
 namespace {
@@ -826,10 +827,7 @@ bool build_cells_and_groups(Tree& t, int32_t* d_stat, hipStream_t st) {
     t.sfirst.alloc(nn, st);
     t.spre.alloc(nn, st);
     t.schild.alloc(nn, st);
-    int uniform_level = 0;   // of a uniform set's leaves
-    while ((n >> (3 * uniform_level)) > t.n_leaf) ++uniform_level;
-    const bool deep = max_level >= uniform_level + kDeepLevels && ng <= kDeepWalkGroups;
-    if ((ng <= kWaveWalkGroups || deep) && nn < kWaveWalkCells) t.srec.alloc(nn, st);
+    if (may_wave_walk(n, ng, t.n_leaf, max_level) && nn < kWaveWalkCells) t.srec.alloc(nn, st);
     for (int L = 0; L <= kLevels; ++L) t.level_off[L] = base.off[L];
     int32_t* sfirst = t.sfirst.get();
     int32_t* spre = t.spre.get();
