@@ -31,6 +31,7 @@
 // Compiled with -ffp-contract=off: the group boxes feed the list decisions,
 // which must be the literal FP64 expressions.
 #include <string>
+#include <type_traits>
 
 #include "common.h"
 #include "walks.h"
@@ -440,7 +441,7 @@ __device__ __forceinline__ uint4 slot_record(const NodeGeo& g, uint32_t a, int k
 // particle lies before the first particle of the next slot of this level.
 // Sums and counts are kept per slot; count, skip link and monopole go to
 // the cell's preorder record, the children get their parent, and the cell
-// its two walk records.
+// its walk records (the one in preorder by k_pack where the tree is large).
 constexpr int kMomLanes = 4;
 
 struct MomentArgs {
@@ -457,18 +458,21 @@ struct MomentArgs {
     uint4* srec;
 };
 
-// Cell i of the slots [lo, hi): a leaf (LEAF), or an inner cell of the level
-// [lo, hi), whose children lie before next_hi; the others are passed by.
-template <bool LEAF>
+// Cell i of the slots [lo, hi): a leaf, or an inner cell of the level [lo, hi),
+// whose children lie before next_hi; those that `CELLS` leaves out are passed
+// by.
+enum Cells { kLeaves = 1, kInner = 2, kAllCells = kLeaves | kInner };
+
+template <int CELLS>
 __device__ __forceinline__ void moments_cell(const MomentArgs& a, int64_t i, int32_t lo, int32_t hi, int32_t next_hi) {
     const int j = threadIdx.x & (kMomLanes - 1);
     const int64_t c = i < hi ? i : lo;
     const int32_t f = a.sfirst[c], pre = a.spre[c], ch = a.schild[c];
-    const bool on = i < hi && (ch < 0) == LEAF;
+    const bool on = i < hi && (CELLS == kAllCells || (ch < 0) == (CELLS == kLeaves)), leaf = ch < 0;
     double sm = 0, sx = 0, sy = 0, sz = 0;
     int64_t cnt = 0;
     int kids = 0;
-    if (LEAF && on) {
+    if ((CELLS & kLeaves) && on && leaf) {
         const int64_t e = pre + 1 < a.nn ? a.pfirst[pre + 1] : a.n;
         for (int64_t s = f + j; s < e; s += kMomLanes) {
             const double mm = a.pm[s];
@@ -480,7 +484,7 @@ __device__ __forceinline__ void moments_cell(const MomentArgs& a, int64_t i, int
         }
         cnt = j == 0 ? e - f : 0;
     }
-    if (!LEAF && on) {
+    if ((CELLS & kInner) && on && !leaf) {
         const int64_t lim = c + 1 < hi ? a.sfirst[c + 1] : a.n;   // first particle of the next cell of this level
         // a cell has at most eight children: two for each lane, loaded together
         int32_t qf[2], qn[2], qp[2];
@@ -528,9 +532,10 @@ __device__ __forceinline__ void moments_cell(const MomentArgs& a, int64_t i, int
         a.rng[pre].count = (int32_t)cnt;
         const int32_t skip = e < a.n ? a.start[e] : (int32_t)a.nn;
         a.rng[pre].skip = skip;
-        const NodeGeo g = a.geo[pre];
-        a.pack[pre] = walk_record(g, (int32_t)cnt, skip);
-        if (a.srec) a.srec[c] = slot_record(g, LEAF ? (uint32_t)cnt : (uint32_t)ch, kids);
+        NodeGeo g;
+        if (CELLS != kAllCells || a.srec) g = a.geo[pre];
+        if (CELLS != kAllCells) a.pack[pre] = walk_record(g, (int32_t)cnt, skip);
+        if (a.srec) a.srec[c] = slot_record(g, leaf ? (uint32_t)cnt : (uint32_t)ch, kids);
         if (pre == 0) a.rng[pre].parent = -1;
         a.oM[pre] = sm;
         a.oX[pre] = sx / sm;
@@ -539,24 +544,39 @@ __device__ __forceinline__ void moments_cell(const MomentArgs& a, int64_t i, int
     }
 }
 
-template <bool LEAF>
+// The walk records of a large tree's cells, in order.
+__global__ __launch_bounds__(256) void k_pack(MomentArgs a) {
+    const int64_t c = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (c < a.nn) a.pack[c] = walk_record(a.geo[c], a.rng[c].count, a.rng[c].skip);
+}
+
+template <int CELLS>
 __global__ __launch_bounds__(256) void k_moments(MomentArgs a, int32_t lo, int32_t hi, int32_t next_hi) {
-    moments_cell<LEAF>(a, lo + blockIdx.x * (int64_t)(256 / kMomLanes) + threadIdx.x / kMomLanes, lo, hi, next_hi);
+    moments_cell<CELLS>(a, lo + blockIdx.x * (int64_t)(256 / kMomLanes) + threadIdx.x / kMomLanes, lo, hi, next_hi);
 }
 
 // Several levels of at most kFewCells cells each, deepest first, by one block:
 // the first levels and, in a clustered set, the last ones, each of which was a
-// launch of its own with a few waves.  The leaves, most of the cells and of the
-// time, come before in one launch, so that a level waits only for its
-// children's sums (10007 clustered particles: 52 us with the leaves among the
-// levels, 33 us).
+// launch of its own with a few waves.
 constexpr int kMomBlock = 1024;
 constexpr int32_t kFewCells = 1024;
+// In trees of at most this many cells the leaves, most of the cells and of the
+// time, come before the levels in one launch, so that a level waits only for
+// its children's sums (10007 clustered particles: 52 us with the leaves among
+// the levels, 33 us).  In larger ones the chip is full either way, and the
+// records, which lie in preorder, are written line by line by a level that has
+// both its kinds of cells at hand, the walk records by a kernel of their own.
+// tree_build with the leaves before / among the levels, us: uniform particles,
+// 262144 with 75000 cells 172 / 185, with 386000 242 / 239, 10^6 with 1.5e6
+// 525 / 491, 8e6 with 1.2e7 3350 / 2750; clustered, 2^20 with 3e5 345 / 345, 8e6
+// with 1.1e7 3400 / 2810.
+constexpr int64_t kLeavesFirst = 3 << 17;
+template <int CELLS>
 __global__ __launch_bounds__(kMomBlock) void k_moments_few(MomentArgs a, LevelBase base, int deepest, int top) {
     for (int L = deepest; L >= top; --L) {
         const int32_t lo = base.off[L], hi = base.off[L + 1], next_hi = L < kMaxLevel ? base.off[L + 2] : hi;
         for (int64_t i = lo; i < hi; i += kMomBlock / kMomLanes)
-            moments_cell<false>(a, i + threadIdx.x / kMomLanes, lo, hi, next_hi);
+            moments_cell<CELLS>(a, i + threadIdx.x / kMomLanes, lo, hi, next_hi);
         __syncthreads();   // the level's sums are read by the next one's cells
     }
 }
@@ -851,22 +871,32 @@ bool build_cells_and_groups(Tree& t, int32_t* d_stat, hipStream_t st) {
     const MomentArgs ma{n, nn, sfirst, spre, schild, pfirst.get(), start.get(), t.px.get(), t.py.get(), t.pz.get(),
                         t.pm.get(), scount.get(), sM.get(), sX.get(), sY.get(), sZ.get(), t.range.get(), t.nM.get(),
                         t.nX.get(), t.nY.get(), t.nZ.get(), t.leaf_of.get(), t.geo.get(), t.pack.get(), t.srec.get()};
-    // the leaves of every level at once, then the inner cells bottom-up
-    hipLaunchKernelGGL(k_moments<true>, dim3(grid_for(nn, 256 / kMomLanes, 1 << 30)), dim3(256), 0, st, ma, 0,
-                       (int32_t)nn, (int32_t)nn);
-    SRF_HIP(hipGetLastError());
     auto cells_of = [&](int L) { return base.off[L + 1] - base.off[L]; };
-    for (int L = max_level - 1; L >= 0; --L) {   // (the deepest level has leaves only)
-        int top = L;   // levels L down to top in one launch
-        while (cells_of(L) <= kFewCells && top > 0 && cells_of(top - 1) <= kFewCells) --top;
-        if (cells_of(L) <= kFewCells) {
-            hipLaunchKernelGGL(k_moments_few, dim3(1), dim3(kMomBlock), 0, st, ma, base, L, top);
-            L = top;
-        } else {
-            const int32_t lo = base.off[L], hi = base.off[L + 1];
-            hipLaunchKernelGGL(k_moments<false>, dim3(grid_for(hi - lo, 256 / kMomLanes, 1 << 30)), dim3(256), 0, st, ma, lo,
-                               hi, L < kMaxLevel ? base.off[L + 2] : hi);
+    // levels `deepest` and up, bottom-up
+    auto levels_up = [&](auto cells, int deepest) {
+        constexpr int CELLS = decltype(cells)::value;
+        for (int L = deepest; L >= 0; --L) {
+            int top = L;   // levels L down to top in one launch
+            while (cells_of(L) <= kFewCells && top > 0 && cells_of(top - 1) <= kFewCells) --top;
+            if (cells_of(L) <= kFewCells) {
+                hipLaunchKernelGGL(k_moments_few<CELLS>, dim3(1), dim3(kMomBlock), 0, st, ma, base, L, top);
+                L = top;
+            } else {
+                const int32_t lo = base.off[L], hi = base.off[L + 1];
+                hipLaunchKernelGGL(k_moments<CELLS>, dim3(grid_for(hi - lo, 256 / kMomLanes, 1 << 30)), dim3(256), 0, st,
+                                   ma, lo, hi, L < kMaxLevel ? base.off[L + 2] : hi);
+            }
+            SRF_HIP(hipGetLastError());
         }
+    };
+    if (nn <= kLeavesFirst) {   // the leaves of every level at once, then the inner cells (the deepest level has none)
+        hipLaunchKernelGGL(k_moments<kLeaves>, dim3(grid_for(nn, 256 / kMomLanes, 1 << 30)), dim3(256), 0, st, ma, 0,
+                           (int32_t)nn, (int32_t)nn);
+        SRF_HIP(hipGetLastError());
+        levels_up(std::integral_constant<int, kInner>{}, max_level - 1);
+    } else {
+        levels_up(std::integral_constant<int, kAllCells>{}, max_level);
+        hipLaunchKernelGGL(k_pack, dim3(grid_for(nn, 256, 1 << 30)), dim3(256), 0, st, ma);
         SRF_HIP(hipGetLastError());
     }
 

@@ -5,8 +5,6 @@ long lists to the waves (down to 0.36 of the threads')."""
 import os
 import subprocess
 
-import pytest
-
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_1211_4406_amd", "csrc")
 UNIFORM = [1, 8, 64, 512, 4096, 32768]
 # n, groups, n_leaf, cutoff (spacings), cells of each level, by waves
@@ -30,24 +28,29 @@ TREES = [
 ]
 
 
-def test_walks_of_timed_trees(tmp_path):
-    src = tmp_path / "walks.cpp"
+def by_waves(trees, where):
+    """Whether waves walk the trees (n, groups, n_leaf, cutoff, theta, cells of each level)."""
+    src = where / "walks.cpp"
     src.write_text(f"""#include "{CSRC}/walks.h"
 #include <cstdio>
 int main() {{
     long long n, ng;
     int leaf, max_level;
-    double rc;
-    while (std::scanf("%lld %lld %d %lf %d", &n, &ng, &leaf, &rc, &max_level) == 5) {{
+    double rc, th;
+    while (std::scanf("%lld %lld %d %lf %lf %d", &n, &ng, &leaf, &rc, &th, &max_level) == 6) {{
         int32_t cells[22] = {{0}};
         for (int L = 0; L <= max_level; ++L) if (std::scanf("%d", &cells[L]) != 1) return 1;
-        std::printf("%d ", srf::may_wave_walk(n, ng, leaf, max_level) && srf::wave_walk(n, ng, cells, max_level, rc, 0.5));
+        std::printf("%d ", srf::may_wave_walk(n, ng, leaf, max_level) && srf::wave_walk(n, ng, cells, max_level, rc, th));
     }}
 }}
 """)
-    exe = str(tmp_path / "walks")
+    exe = str(where / "walks")
     subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-o", exe, str(src)], check=True)
-    rows = "\n".join(" ".join(str(v) for v in (n, ng, leaf, rc * n ** (-1 / 3), len(c) - 1, *c))
-                     for n, ng, leaf, rc, c, _ in TREES)
+    rows = "\n".join(" ".join(str(v) for v in (n, ng, leaf, rc, th, len(c) - 1, *c)) for n, ng, leaf, rc, th, c in trees)
     out = subprocess.run([exe], input=rows, capture_output=True, text=True, check=True).stdout.split()
-    assert [v == "1" for v in out] == [t[-1] for t in TREES]
+    return [v == "1" for v in out]
+
+
+def test_walks_of_timed_trees(tmp_path):
+    got = by_waves([(n, ng, leaf, rc * n ** (-1 / 3), 0.5, c) for n, ng, leaf, rc, c, _ in TREES], tmp_path)
+    assert got == [t[-1] for t in TREES]
