@@ -18,8 +18,8 @@
 // coefficients, and 0 at and beyond r_cut through the clamp of t.
 //
 // Three kernels: mark the cells that occur in some list, their second
-// moments (FP64, 64 cells per wave), and the correction pass (one wave per
-// group, targets in lanes, the list's cells compacted into LDS in chunks of
+// moments (FP64, 64 cells per wave), and the correction pass (one to eight waves
+// per group, targets in lanes, the list's cells compacted into LDS in chunks of
 // 256 entries, split near/far as in the force kernel), which adds G times
 // the term to the accelerations.
 #include "common.h"
@@ -250,9 +250,12 @@ struct QuadShared {
 // A block of W waves takes one group, its chunks dealt to the waves, whose
 // FP64 sums are added in order.  Cells that reach no target of the group,
 // whose terms are exactly zero, are left out of a chunk.
-// Force with quadrupoles, whole pass, with one wave and all cells / so: 518 /
-// 420 us at 20001 clustered particles, 789 / 735 at 131071, 1683 / 1620 at
-// 524287, 5.37 / 5.25 ms at 2^21.
+// The pass with one wave and all cells / so, us: 130 / 76 at 10007 clustered
+// particles, 264 / 195 at 131071, 500 / 380 at 524287, 1923 / 1518 at 2^21.
+// Groups go to the XCDs in turn: with a contiguous run of them each, an XCD with
+// clusters works on while the others wait (524287 clustered particles at a
+// cutoff of 2.75 spacings 296 us, in turn 263; lattice and uniform sets gain 2-3
+// % from the runs, 683 and 695 us at 2^21).
 template <class T, int W>
 __global__ __launch_bounds__(64 * W) void k_quadrupole(
     const int32_t* __restrict__ gfirst, const int32_t* __restrict__ gcount, const double* __restrict__ glo,
@@ -264,7 +267,7 @@ __global__ __launch_bounds__(64 * W) void k_quadrupole(
     using V4 = typename QV4<T>::type;
     using V2 = typename QV2<T>::type;
     __shared__ QuadShared<T> sh_all[W];
-    const int64_t g = xcd_block(blockIdx.x, gridDim.x);
+    const int64_t g = blockIdx.x;
     const int lane = threadIdx.x & 63;
     const int wave = W == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     QuadShared<T>& sh = sh_all[wave];
