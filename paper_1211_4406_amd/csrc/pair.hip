@@ -942,7 +942,13 @@ struct Targets {
 // Dropped entries and masks, adjoint kernel at r_cut of 6 spacings: 25.8 ->
 // 24.8 ms on the 2^24 lattice (15% of the far entries dropped, 11% of the far
 // blocks' targets skipped; without the masks 26.5 ms), 2.93 -> 2.42 ms on the
-// 2^20 clustered set (a quarter and a third).
+// 2^20 clustered set (a quarter and a third).  Groups of one or two target
+// blocks have no masks, which cost them more than they skip (groups of at most
+// 32 targets, us with / without: 420 / 383 at 131071 clustered particles, 1155 /
+// 1127 at 524287, 500 / 461 at 262144 on the lattice, where neither dropping
+// nor masks took 478).
+template <int NB>
+constexpr bool masked() { return NB > 2; }
 constexpr int kAdjSlots = kTile + kRows;
 
 struct Staged {
@@ -985,7 +991,7 @@ __device__ __forceinline__ Staged stage_adjoint(const int32_t* __restrict__ ent,
             tile[pos] = e;
             ids[pos] = v >= 0 ? v : n_part + (-v - 1);
         }
-        if (keep) {
+        if (masked<NB>() && keep) {
             uint32_t bits = 0;
 #pragma unroll
             for (int ib = 0; ib < NB; ++ib) {
@@ -1016,7 +1022,7 @@ __device__ __forceinline__ Staged stage_adjoint(const int32_t* __restrict__ ent,
             const int pos = kAdjSlots - 1 - (4 * r + q);
             tile[pos] = z;
             ids[pos] = -1;
-            smask[pos] = 0;
+            if (masked<NB>()) smask[pos] = 0;
         }
     if (lane < kRows && nnear + lane < kAdjSlots - 4 * most) {
         tile[nnear + lane] = z;
@@ -1067,11 +1073,11 @@ __device__ __forceinline__ void adjoint_entries(int b, int vmask, int slot0, con
             p.w = e < b ? p.w : T(0);
             v = ids[e];
         }
-        const int mask = NEAR ? -1 : __builtin_amdgcn_readlane(vmask, blocks - 1 - blk);
+        const int mask = NEAR || !masked<NB>() ? -1 : __builtin_amdgcn_readlane(vmask, blocks - 1 - blk);
         T jx = T(0), jy = T(0), jz = T(0), jm = T(0);
 #pragma unroll
         for (int ib = 0; ib < NB; ++ib) {
-            if (!NEAR && !(mask & (1 << ib))) continue;
+            if (!NEAR && masked<NB>() && !(mask & (1 << ib))) continue;
             const T dx = p.x - tg.x[ib], dy = p.y - tg.y[ib], dz = p.z - tg.z[ib];
             // the far path with r from s needs no unsoftened r^2: s^2 directly
             const bool direct = !NEAR && RS;
@@ -1176,6 +1182,7 @@ __device__ __forceinline__ void adjoint_group(const GroupArgs& ga, const Src& sr
         tg.wy[ib] = on ? (T)wy[wi] : T(0);
         tg.wz[ib] = on ? (T)wz[wi] : T(0);
         tg.id[ib] = on ? first + i : INT32_MIN;   // INT32_MIN is no list value
+        if (!masked<NB>()) continue;
         // the block's box (targets past the group's last leave it out)
         const float px = (float)tg.x[ib], py = (float)tg.y[ib], pz = (float)tg.z[ib];
         const float lx = row_min(on ? px : INFINITY), ux = -row_min(on ? -px : INFINITY);
@@ -1197,7 +1204,7 @@ __device__ __forceinline__ void adjoint_group(const GroupArgs& ga, const Src& sr
         lds_order();
         // lane i: the target blocks that far block i (from the end) can reach
         uint32_t vm = 0;
-        if (lane < stg.blocks) vm = *reinterpret_cast<const uint32_t*>(sh.smask + kAdjSlots - kRows * (lane + 1));
+        if (masked<NB>() && lane < stg.blocks) vm = *reinterpret_cast<const uint32_t*>(sh.smask + kAdjSlots - kRows * (lane + 1));
         vm |= vm >> 16;
         vm |= vm >> 8;
 #pragma unroll
@@ -1247,6 +1254,12 @@ __device__ __forceinline__ void adjoint_group(const GroupArgs& ga, const Src& sr
     }
 }
 
+// Four waves a SIMD although some 20 to 30 registers of a lane are spilled for
+// them, about 9 GB of traffic a launch at 2^24: three spill nothing and take 8-11
+// % longer on groups of at most 32 targets (us with four / three: 333 / 373 at
+// 131071 clustered particles, 1145 / 1258 at 524287, 1846 / 1985 at 10^6
+// uniform), and as long on groups of 64 (25.28 / 25.26 ms at 2^24 on the
+// lattice, 18.71 / 18.97 at 1.3e7 clustered).
 template <class T, bool RS, int W>
 __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 1))) void k_adjoint(
     GroupArgs ga, Src src, AdjCoef<T> c, const double* __restrict__ wx, const double* __restrict__ wy,
