@@ -413,7 +413,7 @@ def main():
     # waves per group by the groups and their lists (csrc/waves.h)
     rs = "true" if 4.0 * ps.params.eps ** 2 / ps.params.r_cut ** 2 <= 5e-4 else "false"
     kernel_names = {"force": f"k_force<float, {waves_per_group(info, 26.0)}, false, {rs}>",
-                    "adjoint": f"k_adjoint<float, {rs}, {waves_per_group(info, 16.0)}>"}
+                    "adjoint": f"k_adjoint<float, {rs}, {waves_per_group(info, 18.0)}>"}
     kname = kernel_names[dominant]
     traffic = None
     executed = {}

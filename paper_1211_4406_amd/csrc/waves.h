@@ -50,7 +50,7 @@ namespace srf {
 constexpr int64_t kEightGroups = 700, kFourGroups = 3000;
 constexpr double kWavePairs = 90.0, kWaveEntries = 700.0;
 // groups per entry of the average list, by kernel
-constexpr double kForceReach = 26.0, kAdjointReach = 16.0, kQuadrupoleReach = 5.0;
+constexpr double kForceReach = 26.0, kAdjointReach = 18.0, kQuadrupoleReach = 5.0;
 
 // ng groups with `entries` list entries and `interactions` (targets x entries)
 // in all.

@@ -56,4 +56,4 @@ def test_waves_of_measured_sets(rule):
     assert got == [w for _, w in SETS]
     for (g, e, i), w in zip(rows, got):
         info = dict(n_groups=g, n_particle_entries=e, n_node_entries=0, interactions=i)
-        assert (bench.waves_per_group(info, 26.0), bench.waves_per_group(info, 16.0)) == w[:2]
+        assert (bench.waves_per_group(info, 26.0), bench.waves_per_group(info, 18.0)) == w[:2]
