@@ -22,28 +22,29 @@ namespace srf {
 // most 1 to 64, cutoffs of 1.6 to 6 spacings): 1-3 % from it on average, and 34 %
 // at most (a 20 us call).  Kernel calls with 1 / 4 / 8 waves, us:
 //   groups  entries  pairs  force FP32      adjoint FP32    potential FP32  force FP64    adjoint FP64
-//   20000   39       0.6    40/94/216       72/154/264      35/77/157       48/126/239    108/273/539
-//   87      262      94     37/29/29        59/58/58        36/28/27        46/33/34      66/62/65
-//   958     246      80     35/32/40        64/64/86        34/32/37        45/48/64      76/98/154
-//   493     323      205    91/45/42        169/87/83       88/44/42        130/58/56     199/100/123
-//   250     1517     949    297/96/73       626/198/147     297/95/74       451/139/123   754/237/197
-//   2061    383      145    58/55/65        90/96/135       54/49/60        94/88/131     120/157/257
-//   3040    1627     1096   411/256/256     831/497/497     418/250/248     734/477/622   1206/829/1003
-//   5340    480      176    92/100/127      149/186/298     85/89/119       181/198/296   247/353/630
-//   6034    730      248    215/158/195     403/328/427     204/138/178     350/295/448   678/628/975
-//   35405   227      40     137/285/543     247/574/1069    117/238/515
-//   11262   573      407    248/280/339     452/567/921     221/233/307
-//   12715   1504     969    870/702/799     1821/1374/1605  831/635/773
-//   21404   1300     978    1009/970/1135   1842/1899/2368  903/833/1106
-//   24459   1626     1089   1504/1366/1519  3003/2662/3085  1434/1202/1476
-//   43303   425      307    519/680/991     1028/1765/3150  425/556/918
-//   50570   1367     886    2327/2302/2823  4620/4778/5980  2248/2201/2895
-// and the quadrupole pass, whose work is the lists' cells alone, FP32 and FP64:
-//   250     1517            120/83/76       152/99/99
-//   3040    1627            229/197/215     364/348/351
-//   6034    730             262/251/317     413/493/494
-//   12715   1504            418/428/547
-//   43303   425             136/198/320
+//   20000   39       0.6    37/89/198       67/128/213      32/70/140       45/115/212      96/232/480
+//   87      262      94     37/29/28        57/54/55        36/28/27        47/33/34        64/61/64
+//   958     246      80     35/33/39        62/59/80        34/31/37        43/47/64        74/94/150
+//   493     323      205    90/46/42        170/84/82       87/43/41        129/60/57       198/102/125
+//   250     1517     949    297/95/73       622/198/146     298/96/74       446/136/123     748/235/197
+//   2061    383      145    57/53/62        88/90/122       53/50/58        94/88/131       124/155/249
+//   3040    1627     1096   412/254/256     843/490/506     411/245/246     727/502/626     1189/862/1016
+//   5340    480      176    94/99/126       142/164/258     82/86/116       179/197/300     237/340/596
+//   6034    730      248    215/156/190     404/304/393     201/138/175     365/302/463     674/624/943
+//   35405   227      40     133/276/535     223/490/897     112/230/492
+//   11262   573      407    249/276/338     455/560/904     219/234/306
+//   12715   1504     969    871/716/809     1753/1407/1574  829/642/771
+//   21404   1300     978    1018/970/1118   1928/1930/2353  922/832/1102
+//   24459   1626     1089   1471/1394/1510  2944/2676/3042  1417/1204/1471
+//   43303   425      307    517/652/990     1045/1737/3093  428/541/919
+//   50570   1367     886    2322/2317/2808  4744/4769/5902  2243/2199/2887
+// and the quadrupole pass, whose work is the lists' cells alone, FP32 and FP64
+// (which takes four for eight):
+//   250     1517            119/82/77       152/100
+//   3040    1627            222/194/212     359/344
+//   6034    730             264/237/301     408/460
+//   12715   1504            380/406/536
+//   43303   425             141/210/350
 // (By the number of groups alone, 8 below 3500 and 4 below 55000, chosen on
 // groups of 64 targets with lists of about 1500 entries, lists of few tiles took
 // up to 2.7 times as long as with one wave.)
