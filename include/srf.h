@@ -164,9 +164,12 @@ int srf_tree_refit(srf_tree* t, const double* x, const double* y, const double* 
  * p must carry the n_group and n_leaf the tree was built with.  The lists
  * belong to this tree: after it is freed they are refused (SRF_EMISMATCH)
  * by every call, even with a new tree at the same address.
- * Synchronises `stream` once (to size the list buffer); up to three times
- * when some group's list holds more leaves and accepted cells than its slot
- * of the scratch memory (4096 in trees of up to 65536 groups, else 2048).
+ * Synchronises `stream` once (to size the list buffer).  A second time when
+ * one wave per group walks the tree and some group fits neither its slot of
+ * the scratch memory (4096 leaves and accepted cells in trees of up to 65536
+ * groups, else 2048) nor, with the cells it still has to look at, the wave's
+ * stack (1536): one thread per group then walks the tree, with slots of 2048
+ * in every tree.  Once more when a list does not fit the slot of that walk.
  * Errors: SRF_EINVAL, SRF_EMISMATCH, SRF_ENOMEM, SRF_EHIP. */
 int srf_make_lists(const srf_tree* t, const srf_params* p, void* stream, srf_lists** out);
 
@@ -189,6 +192,9 @@ int srf_short_range_force(const srf_tree* t, const srf_lists* l, const srf_param
  *   dL/dx_i -> (gx, gy, gz)[i*g_stride],  dL/dm_i -> gm[i*gm_stride],
  * in input order; w_i = (wx, wy, wz)[i*w_stride].  Node sources pass their
  * gradient to member particles through M_c = sum m_k, X_c = sum m_k x_k / M_c.
+ * A non-finite w_i makes the gradients of particle i, and of what of its list
+ * lies within its reach, non-finite; entries that no target of the group can
+ * reach within r_cut (their derivatives are exactly 0) are not visited.
  * Same parameter rules as srf_short_range_force.  Asynchronous on `stream`;
  * uses FP64 atomics, so the result is reproducible only to rounding.
  * Errors: SRF_EINVAL (also when n + number of cells exceeds 2^31 - 1),

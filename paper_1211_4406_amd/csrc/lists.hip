@@ -1,13 +1,20 @@
 // Step a6: per-group interaction lists (Barnes' modified traversal with the
 // cutoff pruning of the short-range part).
 //
-// Threads walk the preorder cell array without a stack: a cell that is
-// pruned, accepted or a leaf is left through its skip link, any other cell
-// is opened by stepping to the next preorder index (its first child).  A
-// count pass sizes the lists, a scan places them, and a write pass emits
-// one item per leaf or accepted cell in DFS order; an expansion pass then
-// writes the entries (a leaf's particles ascending, cells in preorder) with
-// one wave per group, so that the list memory is written in whole lines.
+// A walk decides for each group which cells are pruned, accepted or opened and
+// which leaves remain, counts the entries, and stores one item per leaf or
+// accepted cell, in DFS order, in the group's slot of a scratch array.  A scan
+// places the lists, and an expansion pass writes the entries (a leaf's
+// particles ascending, cells in preorder) with one wave per group, so that the
+// list memory is written in whole lines.
+//
+// Usually one wave walks for each group, with a stack in LDS (k_walk).  Large
+// trees with short lists, and those where some group fits neither its slot nor
+// the stack, are walked by one thread per group (k_lists; walks.h has the rule)
+// without a stack, over the preorder cell array: a cell that is pruned, accepted
+// or a leaf is left through its skip link, any other cell is opened by stepping
+// to the next preorder index (its first child).  When a list does not fit the
+// slot of that walk, a second one stores every group's items compactly.
 //
 // Compiled with -ffp-contract=off: the decisions are the literal FP64
 // expressions, evaluated in this order:

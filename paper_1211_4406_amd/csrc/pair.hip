@@ -1,11 +1,12 @@
 // Steps a7-a9: the short-range pair kernel (force and adjoint).
 //
-// One 64-lane wavefront handles one group.  The group's particles sit in
+// One 64-lane wavefront handles one group (several in small trees and for long
+// lists, waves.h).  The group's particles sit in
 // registers as offsets from the group centre c_g; the group's list is
 // streamed through LDS in tiles of kTile entries, each entry converted once
 // (in FP64) to the offset x_j - c_g - rint(x_j - c_g) and stored with its
-// mass.  (In trees of few groups several waves share a group, each with
-// tiles, or chunks of them, of its own.)  With N_i particles in the group, the wave runs S = floor(64/N_i)
+// mass.  (Waves that share a group have tiles, or chunks of them, of their own.)
+// With N_i particles in the group, the wave runs S = floor(64/N_i)
 // independent j-streams (lane = i + N_i * stream), whose FP64 partial sums
 // are added at the end; the force's lanes take (chunk, target) pairs instead
 // where N_i is 33 to 50.  Each staged tile is split into near entries (some
@@ -1254,9 +1255,10 @@ __device__ __forceinline__ void adjoint_group(const GroupArgs& ga, const Src& sr
     }
 }
 
-// Four waves a SIMD although some 20 to 30 registers of a lane are spilled for
-// them, about 9 GB of traffic a launch at 2^24: three spill nothing and take 8-11
-// % longer on groups of at most 32 targets (us with four / three: 333 / 373 at
+// Four waves a SIMD although some 30 registers of a lane are spilled for them
+// (at 2^24 a launch reads 7.8 and writes 16.7 GB, 4.2 and 11.7 before the masks
+// brought most of the spills): three spill nothing and take 8-11 % longer on
+// groups of at most 32 targets (us with four / three: 333 / 373 at
 // 131071 clustered particles, 1145 / 1258 at 524287, 1846 / 1985 at 10^6
 // uniform), and as long on groups of 64 (25.28 / 25.26 ms at 2^24 on the
 // lattice, 18.71 / 18.97 at 1.3e7 clustered).
