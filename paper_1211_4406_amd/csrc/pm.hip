@@ -128,8 +128,8 @@ __device__ __forceinline__ int next_piece(const MeshBox* parts, int part, int n_
 // A lane ends with one point's sum.  A workgroup takes kChunk particles in
 // pieces whose box of mesh points fits kBoxMax points, adds the runs' sums to
 // the box in LDS and the box to the mesh with one global atomic per touched
-// point; where even one part's box does not fit, the runs' sums go to the
-// mesh directly.
+// point; where even one part's box does not fit, or the particles are few and
+// spread, the runs' sums go to the mesh directly.
 //   With each particle's 27 products added to the box by LDS atomics, which
 // serialise over the particles of a cell, and one box per workgroup, which half
 // the workgroups' particles did not fit, the kernel took 1.97 ms for 2^24
@@ -143,6 +143,18 @@ constexpr int kAssignThreads = 64 * kAssignWaves;
 // 4096 a workgroup, 106 us with 512).
 constexpr int kChunk = 4096;
 constexpr int kBlocks = 512;
+// With fewer than kFewToAssign particles half the CUs or more are idle, and what
+// counts is the time of one workgroup: up to eight boxes cleared and written
+// one after the other, where particles that moved since their tree was made
+// spread the parts.  A workgroup then takes a box only if one of kFewBox points,
+// as many as it has particles, holds all of them.  The call, with the pieces'
+// boxes and so: uniform, moved by 3 cells of the mesh, 10000 on 16^3 196 us and
+// 118, 40000 on 32^3 209 and 127; in mesh order 127 and 112; 65000 moved on 32^3
+// 209 and 138.  Clusters keep their box: 65000 with a spread of 0.01 on 16^3
+// 90 us, 106 without any.  From 80000 on, boxes gain or cost nothing in order
+// (200000 on 64^3 157 us, 204 without).
+constexpr int64_t kFewToAssign = 1 << 16;
+constexpr int kFewBox = 512;
 constexpr int kBoxMax = 3328;   // FP64 values in LDS (two workgroups per CU)
 constexpr int kWtRow = 68;      // 64 particles, padded: a block's reads fall on distinct banks
 
@@ -172,6 +184,10 @@ __global__ __launch_bounds__(kAssignThreads) void k_tsc_assign(int64_t np, const
     const double* wy = wts[wave][1][kb] + kp;
     const double* wz = wts[wave][2][kb] + kp;
     __syncthreads();
+    if (np < kFewToAssign && most > 0) {   // the same for all waves: parts is shared
+        MeshBox all;
+        if (next_piece(parts, 0, n_parts, 4, kFewBox, all) < n_parts || all.points(4) > kFewBox) most = 0;
+    }
     for (int part = 0; part < n_parts;) {
         MeshBox box;
         const int end = next_piece(parts, part, n_parts, 4, most, box);
