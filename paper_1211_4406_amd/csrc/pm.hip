@@ -146,15 +146,13 @@ constexpr int kBlocks = 512;
 // With fewer than kFewToAssign particles half the CUs or more are idle, and what
 // counts is the time of one workgroup: up to eight boxes cleared and written
 // one after the other, where particles that moved since their tree was made
-// spread the parts.  A workgroup then takes a box only if one of kFewBox points,
-// as many as it has particles, holds all of them.  The call, with the pieces'
-// boxes and so: uniform, moved by 3 cells of the mesh, 10000 on 16^3 196 us and
-// 118, 40000 on 32^3 209 and 127; in mesh order 127 and 112; 65000 moved on 32^3
-// 209 and 138.  Clusters keep their box: 65000 with a spread of 0.01 on 16^3
-// 90 us, 106 without any.  From 80000 on, boxes gain or cost nothing in order
-// (200000 on 64^3 157 us, 204 without).
+// spread the parts.  A workgroup then takes a box only if one holds all its
+// particles.  The call, with the pieces' boxes and so: uniform, moved by 3 cells
+// of the mesh, 10000 on 16^3 196 us and 118, 40000 on 32^3 209 and 127; in mesh
+// order 127 and 112; 65000 moved on 32^3 209 and 137.  Clusters keep their box:
+// 65000 with a spread of 0.01 on 16^3 90 us, 106 without any.  From 80000 on,
+// boxes gain or cost little in order (200000 on 64^3 157 us, 204 without).
 constexpr int64_t kFewToAssign = 1 << 16;
-constexpr int kFewBox = 512;
 constexpr int kBoxMax = 3328;   // FP64 values in LDS (two workgroups per CU)
 constexpr int kWtRow = 68;      // 64 particles, padded: a block's reads fall on distinct banks
 
@@ -184,19 +182,17 @@ __global__ __launch_bounds__(kAssignThreads) void k_tsc_assign(int64_t np, const
     const double* wy = wts[wave][1][kb] + kp;
     const double* wz = wts[wave][2][kb] + kp;
     __syncthreads();
-    if (np < kFewToAssign && most > 0) {   // the same for all waves: parts is shared
-        MeshBox all;
-        if (next_piece(parts, 0, n_parts, 4, kFewBox, all) < n_parts || all.points(4) > kFewBox) most = 0;
-    }
     for (int part = 0; part < n_parts;) {
         MeshBox box;
-        const int end = next_piece(parts, part, n_parts, 4, most, box);
+        int end = next_piece(parts, part, n_parts, 4, most, box);
+        const bool spread = np < kFewToAssign && end < n_parts;   // seen at the first piece
+        if (spread) end = n_parts;
         const int64_t s0 = c0 + part * per;
         const int cnt = (int)((c0 + end * per < c1 ? c0 + end * per : c1) - s0);
         part = end;
         const int bd1 = box.hi[1] - box.lo[1] + 4, bd2 = box.hi[2] - box.lo[2] + 4;
         const int64_t vol = box.points(4);
-        const bool boxed = vol <= most;
+        const bool boxed = vol <= most && !spread;
         double* my_sum = sum_at + (ka * bd1 + kp) * bd2 + kb;
         if (boxed) {
             __syncthreads();   // the last piece's box has been read

@@ -1,5 +1,5 @@
 """The PM step on either side of the 65536 particles from which the assignment
-takes boxes of pieces, and below, where it takes one small box or none: uniform and clustered sets, in mesh order, drifted by a
+takes boxes of pieces, and below, where it takes one box or none: uniform and clustered sets, in mesh order, drifted by a
 cell of the mesh since their tree was made, and in no order.  Both sides compute
 in FP64 with the same formulas and differ by the FFT's and the sums' order:
 1e-10 of the force's norm, as for the other PM tests."""
